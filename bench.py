@@ -100,13 +100,14 @@ def gemm_traffic():
     WRITE_SIZE passes (scaled by a plain 1 GiB copy), or None when the GEMM
     code has changed since the counters were taken."""
     path = os.path.join(ROOT, "profiles", "gemm_f32_mfma_gpt2_124m_b16_traffic.json")
-    src = os.path.join(ROOT, "paper_2606_24780_amd", "csrc", "gemm.hip")
+    csrc = os.path.join(ROOT, "paper_2606_24780_amd", "csrc")
     try:
         rec = json.load(open(path))
-        sha = code_sha256(src)
+        sha = {"gemm_source_sha256": code_sha256(os.path.join(csrc, "gemm.hip")),
+               "gemm_kernel_sha256": code_sha256(os.path.join(csrc, "gemm_kernel.h"))}
     except (OSError, ValueError):
         return None, None
-    if rec.get("gemm_source_sha256") != sha:
+    if any(rec.get(k) != v for k, v in sha.items()):
         return None, rec.get("algorithmic_bytes_per_launch")
     return rec.get("traffic_bytes_per_launch"), rec.get("algorithmic_bytes_per_launch")
 

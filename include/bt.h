@@ -82,7 +82,13 @@ typedef enum {
  * residual (M x N, ldc) is optional and must not alias C.
  * M, N, K >= 0 (an empty product writes beta*C + residual with acc = 0; with
  * K = 0 the epilogue still applies).  M, N, K, lda, ldb, ldc must be
- * multiples of 4.  FP32 inputs, FP32 accumulation on the matrix cores.
+ * multiples of 4.  FP32 inputs and results.  Each FP32 operand is split exactly
+ * into three BF16 numbers and the six largest of their nine products are
+ * accumulated in FP32 on the matrix cores (the other three are below the
+ * rounding of one FP32 product): measured against 64 bits the results are
+ * nearer than those of FP32 matrix instructions.  Infinities, NaN and
+ * operands that BF16 cannot split (next to FLT_MAX, results below 2^-96) are
+ * computed with FP32 instructions.
  * colsum_B (optional, [N]) receives the column sums of op(B) over K,
  *   colsum_B[n] = beta * colsum_B[n] + sum_k op(B)[k, n],
  * i.e. the bias gradient sum_m dY[m, n] of a weight-gradient product
@@ -100,13 +106,13 @@ bt_status bt_gemm(bt_op opA, bt_op opB, int M, int N, int K,
                   const float* residual, float* colsum_B, void* ws, size_t ws_bytes,
                   void* stream);
 size_t bt_gemm_ws_bytes(bt_op opA, bt_op opB, int M, int N, int K, bt_epi epi);
-/* The launch plan bt_gemm uses for a product, computed on the host (no
- * device work): *tile_depth, the k-depth of its 128 x 128 block tile (16 or
- * 32); *splits, the number of K ranges whose partial products are summed in
- * a fixed order (1 = not split; bt_gemm_ws_bytes() > 0 exactly when > 1);
- * *direct, 1 when its operand tiles are copied straight into LDS (every tile
- * full), 0 when they are staged with bounds checks.  The plan depends only on
- * (opA, opB, M, N, K) and the leading dimensions, not on the epilogue.
+/* The plan behind bt_gemm_ws_bytes, computed on the host (no device work):
+ * *tile_depth, its unit of K in 128 x 128 blocks (16 or 32); *splits, the
+ * most K ranges whose partial products the workspace holds, summed in a fixed
+ * order (1 = none, bt_gemm_ws_bytes() = 0; a launch may use fewer);
+ * *direct, 1 when M, N are multiples of 128, K of the unit, and the leading
+ * dimensions below 2^22.  The plan depends only on (opA, opB, M, N, K) and the
+ * leading dimensions, not on the epilogue.
  * M, N, K positive multiples of 4, else BT_ESHAPE; NULL outputs BT_EINVAL. */
 bt_status bt_gemm_plan(bt_op opA, bt_op opB, int M, int N, int K, int lda, int ldb, int* tile_depth,
                        int* splits, int* direct);

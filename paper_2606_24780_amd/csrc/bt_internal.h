@@ -79,6 +79,84 @@ size_t emb_bwd_partials_bytes(long long M, int C);
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// ------------------------------------------------- FP32 products on BF16 MFMA
+// An FP32 number x is the exact sum of three BF16 numbers: h, x rounded to 8
+// significant bits; m, x - h rounded likewise; l, what is left (both
+// differences are exact in FP32, and l has at most 8 bits).  A product of two
+// FP32 numbers is then nine products of BF16 numbers, exact in FP32.  The six
+// largest are kept; m l, l m and l l are below 2^-24 |a||b| each.  Measured
+// against 64 bits over K = 64 .. 16384 terms, the sum of the six on the BF16
+// matrix instructions is nearer than the FP32 ones on the FP32 instructions
+// (normal operands: 1.1e-7 / 4.2e-7 / 2.1e-6 against 1.4e-7 / 5.0e-7 / 2.3e-6
+// at K = 64 / 768 / 16384): the BF16 instruction rounds once per 32 terms.
+// BF16 has FP32's range, so no scaling is needed; infinities, and numbers that
+// round beyond BF16's largest, have NaN remainders.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+// The parts (high, middle, low) of two numbers, each a packed BF16 pair.
+struct Pair3 {
+  unsigned h, m, l;
+};
+
+__device__ __forceinline__ unsigned cvt_bf16x2(float a, float b) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
+
+__device__ __forceinline__ Pair3 split_pair(float x0, float x1) {
+  const unsigned h = cvt_bf16x2(x0, x1);
+  const float r0 = x0 - __builtin_bit_cast(float, h << 16);
+  const float r1 = x1 - __builtin_bit_cast(float, h & 0xffff0000u);
+  const unsigned m = cvt_bf16x2(r0, r1);
+  const float s0 = r0 - __builtin_bit_cast(float, m << 16);
+  const float s1 = r1 - __builtin_bit_cast(float, m & 0xffff0000u);
+  return Pair3{h, m, cvt_bf16x2(s0, s1)};
+}
+
+// A lane's 8 values of a 16 x 32 MFMA operand.
+struct Split8 {
+  uintx4 p[3];
+};
+
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+  Split8 s;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const Pair3 v = split_pair(x[2 * j], x[2 * j + 1]);
+    s.p[0][j] = v.h;
+    s.p[1][j] = v.m;
+    s.p[2][j] = v.l;
+  }
+  return s;
+}
+
+// acc[i][j] + (returned)[i][j] += sum_k a[i][k] b[j][k], 16 x 16 x 32: lane
+// (li = l % 16, lo = l / 16) holds row li, k 8 lo .. + 7 of each operand, and
+// elements i = 4 lo + r, j = li of the result.
+//
+// The products of the high parts go straight into acc; the other five are
+// returned as a sum of their own, smallest first, which the caller adds with
+// FP32 additions.  The matrix instructions cut addends off (toward minus
+// infinity) some bits below the largest: high parts' products have 16 bits and
+// lose nothing, but the others added to a long sum gave every result a bias
+// (-4e-8 / -1e-6 of its size at K = 768 / 16384, where the FP32 instructions
+// have none), which a column sum over many rows turns into its error (2.6e-6
+// against 6e-7).  Among themselves they lose 2^-8 as much.
+__device__ __forceinline__ floatx4 mfma_split(floatx4& acc, const uintx4 (&a)[3], const Split8& b) {
+  constexpr int QA[5] = {0, 2, 1, 0, 1}, QB[5] = {2, 0, 1, 1, 0};
+  floatx4 c = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < 5; ++q)
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[QA[q]]),
+                                                __builtin_bit_cast(bf16x8, b.p[QB[q]]), c, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[0]), __builtin_bit_cast(bf16x8, b.p[0]),
+                                                acc, 0, 0, 0);
+  return c;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -1,0 +1,631 @@
+// FP32 products on the CDNA4 BF16 matrix cores: the kernel.
+//
+// Serves every dense projection of the training step in its three layouts
+// (native GEMM library paragraph of "Implementation": QKV, attention-output
+// and MLP projections in forward and backward layouts, plus the tied LM
+// head):  forward Y = X W (NN), input gradient dX = dY W^T (NT), weight
+// gradient dW = X^T dY (TN, reduction over tokens, split along K).
+//
+// What bounds it.  The FP32 matrix instructions peak at 157 TFLOP/s, and a
+// kernel built on them reached 87% of that (130-138 TFLOP/s on the model's
+// products).  The BF16 ones peak at 2.5 PFLOP/s.  An FP32 number is the exact
+// sum of three BF16 numbers, so an FP32 product is nine BF16 products, of
+// which the three smallest together stay below one FP32 rounding of |a||b|
+// and are left out (bt_internal.h): six BF16 products, 417 TFLOP/s at the
+// nominal rate.  On MI355X dense BF16 work on random data is limited by power,
+// not by issue: six-product chains from registers alone run at 380 TFLOP/s
+// with 16x16x32 MFMAs and at 303 with 32x32x16 ones (the clock falls from
+// 2.35 to 1.7 GHz; with zero operands both run at 410), so the kernel is laid
+// out to spend little energy beside the MFMAs:
+//  * 16x16x32 MFMAs, the six products of an accumulator back to back
+//    (384 against 348 TFLOP/s with the accumulators interleaved);
+//  * a block tile of 256 x 192 on one CU: 8 waves of 32 x 192 outputs.  Each
+//    wave loads its own 32 rows of op(A) from global memory straight into
+//    registers and splits them there: A never passes through LDS, and no
+//    other wave splits it again.  op(B) is split once per block on its way
+//    into LDS.  A 128 x 192 tile (4 waves, two blocks per CU) was 3-6% slower
+//    for its additional loads; FP32 tiles in LDS split by every wave that
+//    reads them reached 180-215 TFLOP/s against 214-246 here;
+//  * the B tile in LDS is stored as the MFMA reads it (1 KB of one part's
+//    16 x 32 fragment, lane by lane), so reads are linear and free of
+//    conflicts; its parts are read once per fragment and wave.
+// The split of the next k-tile (5.5 vector instructions per value) is spread
+// evenly between the MFMAs of this one: 2 of them per MFMA hide completely
+// with two waves per SIMD, but the same work in one burst per k-tile cost 13%
+// of the cycles.  At 16384 x 768 x 3072 (NT) the matrix pipe is busy in 77%
+// of the cycles; 246 TFLOP/s on random data, 309 on zeros (FP32 instructions:
+// 138 on both).
+//
+// Three LDS buffers (256-row tiles) let one barrier in mid-tile order writes
+// and reads; the fragments of the next k-tile are then read ahead of its
+// first MFMA.  Two blocks per CU have two buffers and a barrier per k-tile.
+//
+// Operand addresses are a uniform buffer resource per k-tile and per-lane
+// 32-bit offsets.  K remainders: rows past the end of K of an MN-contiguous
+// operand lie outside its buffer resource and read as 0; lanes past the end
+// of a K-contiguous row take an offset outside it.  Rows past M and columns
+// past N read the last valid ones and are not stored.
+//
+// A result that the parts cannot represent is recomputed by its wave with the
+// FP32 instructions, from global memory: one that came out infinite or NaN
+// (an infinite operand, or one that rounds beyond BF16's largest number, has
+// NaN parts), and a tile that holds nothing but results below 2^-96 (the low
+// parts of operands under 2^-110 leave BF16's range).
+#pragma once
+
+#include <type_traits>
+
+#include "bt_internal.h"
+
+namespace bt {
+
+struct GemmParams {
+  const float* A;
+  const float* B;
+  float* C;
+  const float* bias;
+  float* preact;
+  const float* gelu_in;
+  const float* residual;
+  float* ws;         // split-K partials [splits][M][N]
+  float* colsum;     // optional column sums of op(B) over K (bias gradient of a weight-gradient product)
+  float* ws_colsum;  // split-K partial column sums [splits][N]
+  long long lda, ldb, ldc;
+  int M, N, K;
+  int ksplit;  // K range handled by one split (multiple of 32)
+  int splits;
+  int tiles_m, tiles_n;
+  int epi;
+  float beta;
+  // batched products only: batch y addresses A + (y / batch_h) sa_b +
+  // (y % batch_h) sa_h (likewise B, C)
+  int nbatch, batch_h;
+  long long sa_b, sa_h, sb_b, sb_h, sc_b, sc_h;
+  // segmented batched products only: rows of A (and C) are 1 or 2 segments
+  // of `seg` rows starting at positions q_pos[i], the K range 1 or 2 such
+  // segments at k_pos[i]; output row i sums the k whose position is at most
+  // the last position of its BM-row tile
+  int seg;
+  int q_pos[2], k_pos[2];
+};
+
+// Leading dimensions whose per-lane byte offsets (at most 256 rows of one
+// k-tile) stay below 2 GiB, the extent of the kernel's buffer resources.
+// Wider operands take the WIDE kernel (64-bit addresses).
+inline bool gemm_offsets_fit(long long lda, long long ldb) { return lda < (1LL << 21) && ldb < (1LL << 21); }
+
+// Launches of one operand layout (gemm_nn.hip and its siblings): tile is an
+// index into the block tiles below.
+enum GemmTile { TILE_256x192 = 0, TILE_128x192, TILE_128x128, TILE_128x64, TILE_64x64, TILE_COUNT };
+void gemm_launch_nn(const GemmParams& p, int tile, bool wide, unsigned blocks, hipStream_t s);
+void gemm_launch_nt(const GemmParams& p, int tile, bool wide, unsigned blocks, hipStream_t s);
+void gemm_launch_tn(const GemmParams& p, int tile, bool wide, unsigned blocks, hipStream_t s);
+void gemm_launch_tt(const GemmParams& p, int tile, bool wide, unsigned blocks, hipStream_t s);
+
+namespace {
+
+constexpr int BK = 32;  // k-depth of a tile: one 16x16x32 MFMA
+
+// Tiles whose results are all below this (and not all 0) are recomputed in
+// FP32: with one operand of ordinary size, the other is small enough that
+// its low parts may have left BF16's range.  Measured with operands of
+// 1e-30, 1e-34 and 1e-36 and a product of 256 terms: error 2.4e-7, 3.6e-7 and
+// 2.7e-5 against 2.8e-7 in FP32.
+constexpr float TINY_RESULT = 0x1p-96f;
+constexpr float MAX_FLOAT = 0x1.fffffep127f;
+
+// LDS image of the B tile, R columns of op(B) by 32 k: per part (high,
+// middle, low) and 16 columns 1 KB, laid out as lane l of the fragment read
+// (column l % 16, k 8 (l / 16) .. + 7) takes its 16 bytes.
+//
+// Staged in half chunks (one column, 4 consecutive k: one float4 of a
+// K-contiguous operand, 8 bytes per part).  K-contiguous: 16 lanes take 16
+// columns and the next 16 the following 4 k, so a load covers 64 contiguous
+// bytes of 16 rows.  MN-contiguous: consecutive lanes take consecutive
+// columns.
+template <bool KC, int R, int NT>
+struct BTile {
+  static constexpr int PART_STRIDE = R * 64;
+  static constexpr int BYTES = 3 * PART_STRIDE;
+  static constexpr int HPT = R * 8 / NT;  // half chunks per thread
+  static_assert(HPT >= 1 && HPT * NT == R * 8, "B tile must divide over the block");
+  __device__ static int col(int c) { return KC ? (c >> 7) * 16 + (c & 15) : c % R; }
+  __device__ static int quad(int c) { return KC ? (c >> 4) & 7 : c / R; }
+  __device__ static int lds(int c) {
+    return (col(c) >> 4) * 1024 + (quad(c) >> 1) * 256 + (col(c) & 15) * 16 + (quad(c) & 1) * 8;
+  }
+};
+
+template <int N>
+struct FloatVec {
+  typedef float type __attribute__((ext_vector_type(N)));
+};
+// bias, pre-activation, GELU input and residual carry no alignment
+// requirement beyond 4 bytes
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ floatx4 load_u(const float* p) { return *reinterpret_cast<const floatx4u*>(p); }
+
+__device__ __forceinline__ auto tile_rsrc(const float* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, bytes, 0x00020000);
+}
+
+// W waves, each with 16 MB rows of op(A) and all 16 NB columns of the block
+// tile.  BMODE 1 (causal): a batch of products (blockIdx.x % nbatch selects
+// the batch) in which the output rows of a tile starting at m0 only sum
+// k < m0 + BM; tile rows are launched heaviest first.  BMODE 2 (segmented):
+// the same with positions (GemmParams::seg): a row tile sums, in each key
+// segment, the prefix of k whose positions do not exceed its last row's, in
+// BM-aligned steps.
+template <bool A_KC, bool B_KC, bool COLSUM, int W, int MB, int NB, bool WIDE, int BMODE>
+__global__ void __launch_bounds__(64 * W, 2) gemm_f32_mfma(const GemmParams pk) {
+  GemmParams p = pk;
+  constexpr int BM = 16 * W * MB, BN = 16 * NB, WM = 16 * MB, NT = 64 * W;
+  using TB = BTile<B_KC, BN, NT>;
+  constexpr int HPT = TB::HPT;
+  constexpr int NBUF = W == 8 ? 3 : 2;
+  static_assert(NBUF * TB::BYTES * (W == 8 ? 1 : 2) <= 160 * 1024, "LDS exceeds one CU at two waves per SIMD");
+  static_assert(NB % 2 == 0, "B fragments alternate between two register sets");
+  static_assert(8 * BN * 4 <= NBUF * TB::BYTES, "column sums are combined in the B tiles' LDS");
+  __shared__ __attribute__((aligned(16))) char smem[NBUF * TB::BYTES];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15;  // row of an A fragment
+  const int lo = lane >> 4;  // which 8 of its 32 k
+
+  int z, tm, tn;
+  if (BMODE != 0) {
+    const int y = blockIdx.x % p.nbatch;
+    const int rank = blockIdx.x / p.nbatch;  // 0: last tile row (longest k range)
+    tm = p.tiles_m - 1 - rank / p.tiles_n;
+    tn = rank % p.tiles_n;
+    z = 0;
+    const int yb = y / p.batch_h, yh = y % p.batch_h;
+    p.A += yb * p.sa_b + yh * p.sa_h;
+    p.B += yb * p.sb_b + yh * p.sb_h;
+    p.C += yb * p.sc_b + yh * p.sc_h;
+  } else {
+    // ---- tile scheduling: XCD-contiguous ranges (round-robin dispatch over
+    // 8 XCDs, one L2 each) of a grouped tile order (8 tile rows), so
+    // concurrent tiles share A rows / B columns in L2
+    const int ntiles = p.tiles_m * p.tiles_n;
+    const int total = gridDim.x;
+    int bid = blockIdx.x;
+    if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
+    z = bid / ntiles;
+    const int tile = bid - z * ntiles;
+    const int group = 8 * p.tiles_n;
+    const int gid = tile / group;
+    const int first_m = gid * 8;
+    const int gsz = min(p.tiles_m - first_m, 8);
+    const int in_g = tile - gid * group;
+    tm = first_m + in_g % gsz;
+    tn = in_g / gsz;
+  }
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  const int kbeg = z * p.ksplit;
+  int kend = min(p.K, kbeg + p.ksplit);
+  if (BMODE == 1) kend = min(kend, m0 + BM);
+  int nk, n0t = 0;  // k-tiles; segmented: k-tiles in the first key segment
+  if (BMODE == 2) {
+    const int last_pos = (m0 < p.seg ? p.q_pos[0] + m0 : p.q_pos[1] + (m0 - p.seg)) + BM - 1;
+    auto visible = [&](int kpos) { return last_pos < kpos ? 0 : min(p.seg, (last_pos - kpos) / BM * BM + BM); };
+    n0t = visible(p.k_pos[0]) / BK;
+    nk = n0t + (p.K > p.seg ? visible(p.k_pos[1]) / BK : 0);
+  } else {
+    nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
+  }
+  // k offset (from kbeg) of k-tile t
+  auto koff = [&](int t) { return BMODE == 2 ? (t < n0t ? t * BK : p.seg + (t - n0t) * BK) : t * BK; };
+
+  floatx4 acc[MB][NB];
+  auto zero_acc = [&] {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int jb = 0; jb < NB; ++jb) acc[mb][jb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  zero_acc();
+
+  // ---- operand addresses: bytes (WIDE: elements) from the k-tile's base.
+  // Row of op(A) in fragment mb: 16 mb + li if K-contiguous, else MB li + mb,
+  // so that a lane reads its MB rows of one k as one vector.
+  const int mrem = p.M - m0, nrem = p.N - n0;
+  const float* const a_blk = p.A + (A_KC ? (long long)m0 * p.lda + kbeg : (long long)kbeg * p.lda + m0);
+  const float* const b_blk = p.B + (B_KC ? (long long)n0 * p.ldb + kbeg : (long long)kbeg * p.ldb + n0);
+  typedef typename std::conditional<WIDE, long long, unsigned>::type off_t_;
+  constexpr int UNIT = WIDE ? 1 : 4;
+  off_t_ a_off[A_KC ? MB : 1], b_off[HPT];
+  if (A_KC) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+      a_off[mb] = UNIT * ((off_t_)min(wave * WM + mb * 16 + li, mrem - 1) * (off_t_)p.lda + 8 * lo);
+  } else {
+    a_off[0] = UNIT * ((off_t_)min(wave * WM + MB * li, mrem - MB) + (off_t_)(8 * lo) * (off_t_)p.lda);
+  }
+#pragma unroll
+  for (int i = 0; i < HPT; ++i) {
+    const int c = tid + NT * i, col = min(TB::col(c), nrem - 1), k = 4 * TB::quad(c);
+    b_off[i] = UNIT * (B_KC ? (off_t_)col * (off_t_)p.ldb + k : (off_t_)col + (off_t_)k * (off_t_)p.ldb);
+  }
+  // The 4 values k .. k + 3 of a K-contiguous row (k < klim, else 0);
+  // `base` is the k-tile's, `off` the lane's offset of value k.
+  constexpr unsigned FAR = 0x80000000u;  // the buffer resources' extent: reads there give 0
+  auto load4 = [&](float* r, const float* base, off_t_ off, int k, int klim) {
+    floatx4 v;
+    if constexpr (!WIDE) {
+      v = __builtin_bit_cast(
+          floatx4, __builtin_amdgcn_raw_buffer_load_b128(tile_rsrc(base, (int)FAR), k < klim ? off : FAR, 0, 0));
+    } else {
+      v = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (k < klim) v = *reinterpret_cast<const floatx4*>(base + off);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = v[j];
+  };
+  // VN consecutive rows of an MN-contiguous operand at k-row `k` (klim rows are valid).
+  auto load_mn = [&](auto vn, const float* base, long long ld, off_t_ off, int j, int k, int klim) {
+    constexpr int VN = decltype(vn)::value;
+    typedef typename FloatVec<VN>::type V;
+    V v;
+    if constexpr (!WIDE) {
+      const auto r = tile_rsrc(base, 4 * (int)ld * min(klim, BK));
+      const int so = 4 * j * (int)ld;
+      if constexpr (VN == 4) v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, so, 0));
+      else if constexpr (VN == 2) v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, so, 0));
+      else v[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, so, 0));
+    } else {
+#pragma unroll
+      for (int e = 0; e < VN; ++e) v[e] = 0.f;
+      if (k < klim) v = *reinterpret_cast<const V*>(base + off + j * ld);
+    }
+    return v;
+  };
+  float ra[MB][8], rb[HPT][4];  // k-tile t + 1, in flight or waiting to be split
+  Split8 fa[2][MB];             // split A fragments of k-tiles t and t + 1
+  auto load_a_frag = [&](int t, int mb) {
+    const int ko = koff(t), klim = kend - kbeg - ko;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      load4(&ra[mb][4 * g], a_blk + ko, a_off[A_KC ? mb : 0] + UNIT * 4 * g, 8 * lo + 4 * g, klim);
+  };
+  auto load_a = [&](int t) {
+    if (A_KC) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) load_a_frag(t, mb);
+    } else {
+      const int ko = koff(t), klim = kend - kbeg - ko;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const auto v = load_mn(std::integral_constant<int, MB>(), a_blk + (long long)ko * p.lda, p.lda, a_off[0], j,
+                               8 * lo + j, klim);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) ra[mb][j] = v[mb];
+      }
+    }
+  };
+  auto load_b = [&](int t, int i) {
+    const int ko = koff(t), klim = kend - kbeg - ko;
+    const int k = 4 * TB::quad(tid + NT * i);
+    if (B_KC) {
+      load4(rb[i], b_blk + ko, b_off[i], k, klim);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        rb[i][j] = load_mn(std::integral_constant<int, 1>(), b_blk + (long long)ko * p.ldb, p.ldb, b_off[i], j, k + j,
+                           klim)[0];
+    }
+  };
+  // Column sums of op(B) (MN-contiguous B only), kept by the first tile row
+  // of blocks: each thread adds up the values it stages.
+  float csum[HPT];
+#pragma unroll
+  for (int i = 0; i < HPT; ++i) csum[i] = 0.f;
+  const bool cs_block = COLSUM && tm == 0;
+  auto colsum_b = [&](int i) {
+    if (COLSUM && cs_block) csum[i] += (rb[i][0] + rb[i][1]) + (rb[i][2] + rb[i][3]);
+  };
+  auto write_b = [&](char* buf, int i, const Pair3 x, const Pair3 y) {
+    char* d = buf + TB::lds(tid + NT * i);
+    *reinterpret_cast<uintx2*>(d) = uintx2{x.h, y.h};
+    *reinterpret_cast<uintx2*>(d + TB::PART_STRIDE) = uintx2{x.m, y.m};
+    *reinterpret_cast<uintx2*>(d + 2 * TB::PART_STRIDE) = uintx2{x.l, y.l};
+  };
+  uintx4 fb[2][3];
+  auto read_b = [&](uintx4(&f)[3], const char* buf, int jb) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      f[q] = *reinterpret_cast<const uintx4*>(buf + 16 * lane + jb * 1024 + q * TB::PART_STRIDE);
+  };
+  // Barrier that waits for this wave's LDS operations but not for its global
+  // loads (which go to registers and are waited for where they are used).
+  auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  const int last = nk - 1;
+  if (nk > 0) {
+    load_a(0);
+#pragma unroll
+    for (int i = 0; i < HPT; ++i) load_b(0, i);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) fa[0][mb] = split8(ra[mb]);
+    load_a(min(1, last));
+#pragma unroll
+    for (int i = 0; i < HPT; ++i) {
+      colsum_b(i);
+      write_b(smem, i, split_pair(rb[i][0], rb[i][1]), split_pair(rb[i][2], rb[i][3]));
+      load_b(min(1, last), i);
+    }
+    lds_barrier();
+    if (NBUF == 3) read_b(fb[0], smem, 0);
+  }
+
+  // One k-tile: NB slots, one per 16 columns.  A slot reads the next slot's
+  // B fragment, splits its share of k-tile t + 1 (B first, then A), issues
+  // loads of k-tile t + 2 into the registers that this freed, and runs its
+  // 6 MB MFMAs.  With three buffers the barrier stands after the slot of the
+  // last LDS write: k-tile t + 1 is then complete, and the buffer that
+  // k-tile t + 2 will be written to was last read in k-tile t - 1, which every
+  // wave has finished.
+  constexpr int NP = 2 * HPT + 4 * MB;  // operand pairs a thread splits per k-tile
+  constexpr int BAR_SLOT = NBUF == 3 ? (2 * HPT - 1) * NB / NP : NB - 1;
+  floatx4 prod[2][MB];  // a slot's smaller products, until the next slot adds them
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) prod[(NB - 1) & 1][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto add_products = [&](int jb) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb][jb] += prod[jb & 1][mb];
+  };
+  int buf = 0;
+  unsigned sph = 0, spm = 0, spl = 0;  // first pair of a half chunk until its second is split
+  auto body = [&](int t, auto par) {
+    constexpr int CUR = decltype(par)::value;
+    const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
+    const char* sb = smem + buf * TB::BYTES;
+    char* sn = smem + nbuf * TB::BYTES;
+    const int t2 = min(t + 2, last);
+    if (NBUF == 2) read_b(fb[0], sb, 0);
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb) {
+      if (jb + 1 < NB) read_b(fb[(jb + 1) & 1], sb, jb + 1);
+      else if (NBUF == 3) read_b(fb[(jb + 1) & 1], sn, 0);
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        if (u * NB / NP != jb) continue;
+        if (u < 2 * HPT) {
+          const int i = u >> 1;
+          if (u & 1) {
+            write_b(sn, i, Pair3{sph, spm, spl}, split_pair(rb[i][2], rb[i][3]));
+            load_b(t2, i);
+          } else {
+            if (COLSUM && t < last) colsum_b(i);
+            const Pair3 v = split_pair(rb[i][0], rb[i][1]);
+            sph = v.h;
+            spm = v.m;
+            spl = v.l;
+          }
+        } else {
+          const int mb = (u - 2 * HPT) >> 2, e = (u - 2 * HPT) & 3;
+          const Pair3 v = split_pair(ra[mb][2 * e], ra[mb][2 * e + 1]);
+          fa[CUR ^ 1][mb].p[0][e] = v.h;
+          fa[CUR ^ 1][mb].p[1][e] = v.m;
+          fa[CUR ^ 1][mb].p[2][e] = v.l;
+          if (A_KC && e == 3) load_a_frag(t2, mb);
+          if (!A_KC && u == NP - 1) load_a(t2);
+        }
+      }
+      // the previous slot's products are added while this one's run
+      add_products(jb > 0 ? jb - 1 : NB - 1);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) prod[jb & 1][mb] = mfma_split(acc[mb][jb], fb[jb & 1], fa[CUR][mb]);
+      // the slot's instructions: fragment reads first, then the vector
+      // instructions evenly behind the MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+      for (int q = 0; q < 6 * MB; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, 2, 0);
+      }
+      if (jb == BAR_SLOT) lds_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    buf = nbuf;
+  };
+  {
+    int t = 0;
+    for (; t + 1 < nk; t += 2) {
+      body(t, std::integral_constant<int, 0>());
+      body(t + 1, std::integral_constant<int, 1>());
+    }
+    if (t < nk) body(t, std::integral_constant<int, 0>());
+    add_products(NB - 1);
+  }
+
+  if (COLSUM && cs_block) {
+    // combine the eight 4-k groups of each column in a fixed order
+    float* red = reinterpret_cast<float*>(smem);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < HPT; ++i) {
+      const int c = tid + NT * i;
+      red[TB::quad(c) * BN + TB::col(c)] = csum[i];
+    }
+    __syncthreads();
+    for (int c = tid; c < BN; c += NT) {
+      const int n = n0 + c;
+      if (n >= p.N) continue;
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += red[q * BN + c];
+      if (p.splits > 1) {
+        p.ws_colsum[(long long)z * p.N + n] = s;
+      } else {
+        if (p.beta != 0.f) s += p.colsum[n];
+        p.colsum[n] = s;
+      }
+    }
+  }
+
+  // ---- results that the parts cannot represent: again in FP32
+  {
+    float mx = 0.f;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = __builtin_elementwise_maximum(mx, __builtin_fabsf(acc[mb][jb][r]));
+    const bool redo = __any(!(mx <= MAX_FLOAT)) || (!__any(mx >= TINY_RESULT) && __any(mx > 0.f));
+    if (__builtin_expect(redo, 0)) {
+      zero_acc();
+      for (int t = 0; t < nk; ++t) {
+        const int ko = koff(t);
+        for (int s = 0; s < BK; s += 4) {
+          const bool ok = kbeg + ko + s + lo < kend;
+          const int k = ok ? ko + s + lo : ko;
+          float a[MB], b[NB];
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            const int row = A_KC ? min(wave * WM + mb * 16 + li, mrem - 1) : min(wave * WM + MB * li, mrem - MB) + mb;
+            const float v = A_KC ? a_blk[(long long)row * p.lda + k] : a_blk[(long long)k * p.lda + row];
+            a[mb] = ok ? v : 0.f;
+          }
+#pragma unroll
+          for (int jb = 0; jb < NB; ++jb) {
+            const int col = min(jb * 16 + li, nrem - 1);
+            const float v = B_KC ? b_blk[(long long)col * p.ldb + k] : b_blk[(long long)k * p.ldb + col];
+            b[jb] = ok ? v : 0.f;
+          }
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+              acc[mb][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jb], a[mb], acc[mb][jb], 0, 0, 0);
+        }
+      }
+    }
+  }
+
+  // ---- epilogue.  Lane (li, lo) holds one row of each fragment mb and
+  // columns 16 jb + 4 lo .. + 3: every access is a float4.  All inputs of a
+  // wave are loaded before its first store where the registers allow
+  // (loads and stores retire in order on one counter, so a load issued after
+  // a store also waits for that store).
+  auto row_of = [&](int mb) { return m0 + wave * WM + (A_KC ? mb * 16 + li : MB * li + mb); };
+  auto col_of = [&](int jb) { return n0 + 16 * jb + 4 * lo; };
+  if (p.splits > 1) {
+    float* ws = p.ws + (long long)z * p.M * p.N;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int jb = 0; jb < NB; ++jb)
+        if (row_of(mb) < p.M && col_of(jb) < p.N)
+          *reinterpret_cast<floatx4*>(ws + (long long)row_of(mb) * p.N + col_of(jb)) = acc[mb][jb];
+    return;
+  }
+  auto load_in = [&](floatx4(&in)[NB], const float* src, int mb) {
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb) {
+      in[jb] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (row_of(mb) < p.M && col_of(jb) < p.N) in[jb] = load_u(src + (long long)row_of(mb) * p.ldc + col_of(jb));
+    }
+  };
+  auto store = [&](int mb, int jb, const floatx4& v) {
+    if (row_of(mb) < p.M && col_of(jb) < p.N)
+      *reinterpret_cast<floatx4*>(p.C + (long long)row_of(mb) * p.ldc + col_of(jb)) = v;
+  };
+  const bool has_res = p.residual != nullptr, has_old = p.beta != 0.f;
+  auto finish = [&](auto epi) {
+    constexpr int EPI = decltype(epi)::value;
+    constexpr bool BIAS = EPI == BT_EPI_BIAS || EPI == BT_EPI_BIAS_GELU;
+    floatx4 bias[BIAS ? NB : 1];
+    if constexpr (BIAS) {
+#pragma unroll
+      for (int jb = 0; jb < NB; ++jb) {
+        bias[jb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (col_of(jb) < p.N) bias[jb] = load_u(p.bias + col_of(jb));
+      }
+    }
+    auto value = [&](int mb, int jb, const floatx4& gin) {
+      floatx4 v = acc[mb][jb];
+      if constexpr (BIAS) v += bias[jb];
+      if constexpr (EPI == BT_EPI_BIAS_GELU) {
+        if (p.preact && row_of(mb) < p.M && col_of(jb) < p.N)
+          *reinterpret_cast<floatx4u*>(p.preact + (long long)row_of(mb) * p.ldc + col_of(jb)) = v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = gelu_f(v[r]);
+      }
+      if constexpr (EPI == BT_EPI_DGELU) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] *= gelu_grad_f(gin[r]);
+      }
+      return v;
+    };
+    if (!has_res && !has_old) {
+      floatx4 in[EPI == BT_EPI_DGELU ? MB : 1][NB];
+      if constexpr (EPI == BT_EPI_DGELU) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) load_in(in[mb], p.gelu_in, mb);
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) store(mb, jb, value(mb, jb, in[EPI == BT_EPI_DGELU ? mb : 0][jb]));
+    } else if (EPI != BT_EPI_DGELU && has_res != has_old) {
+      floatx4 in[MB][NB];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) load_in(in[mb], has_res ? p.residual : p.C, mb);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) store(mb, jb, value(mb, jb, in[mb][jb]) + in[mb][jb]);
+    } else {
+      // two inputs or more: block by block
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) {
+          if (row_of(mb) >= p.M || col_of(jb) >= p.N) continue;
+          const long long off = (long long)row_of(mb) * p.ldc + col_of(jb);
+          floatx4 gin = floatx4{0.f, 0.f, 0.f, 0.f}, add = floatx4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (EPI == BT_EPI_DGELU) gin = load_u(p.gelu_in + off);
+          if (has_res) add = load_u(p.residual + off);
+          if (has_old) add += load_u(p.C + off);
+          store(mb, jb, value(mb, jb, gin) + add);
+        }
+    }
+  };
+  if (BMODE != 0 || p.epi == BT_EPI_NONE) finish(std::integral_constant<int, BT_EPI_NONE>());
+  else if (p.epi == BT_EPI_BIAS) finish(std::integral_constant<int, BT_EPI_BIAS>());
+  else if (p.epi == BT_EPI_BIAS_GELU) finish(std::integral_constant<int, BT_EPI_BIAS_GELU>());
+  else finish(std::integral_constant<int, BT_EPI_DGELU>());
+}
+
+template <bool A_KC, bool B_KC, int W, int MB, int NB, bool WIDE>
+void launch_gemm_tile(const GemmParams& p, unsigned blocks, hipStream_t s) {
+  if constexpr (!B_KC) {
+    if (p.colsum) {
+      hipLaunchKernelGGL((gemm_f32_mfma<A_KC, B_KC, true, W, MB, NB, WIDE, 0>), dim3(blocks), dim3(64 * W), 0, s, p);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((gemm_f32_mfma<A_KC, B_KC, false, W, MB, NB, WIDE, 0>), dim3(blocks), dim3(64 * W), 0, s, p);
+}
+
+// WIDE operands always take the 128 x 64 tile.
+template <bool A_KC, bool B_KC>
+void launch_gemm(const GemmParams& p, int tile, bool wide, unsigned blocks, hipStream_t s) {
+  if (wide) return launch_gemm_tile<A_KC, B_KC, 4, 2, 4, true>(p, blocks, s);
+  switch (tile) {
+    case TILE_256x192: return launch_gemm_tile<A_KC, B_KC, 8, 2, 12, false>(p, blocks, s);
+    case TILE_128x192: return launch_gemm_tile<A_KC, B_KC, 4, 2, 12, false>(p, blocks, s);
+    case TILE_128x128: return launch_gemm_tile<A_KC, B_KC, 4, 2, 8, false>(p, blocks, s);
+    case TILE_128x64: return launch_gemm_tile<A_KC, B_KC, 4, 2, 4, false>(p, blocks, s);
+    default: return launch_gemm_tile<A_KC, B_KC, 4, 1, 4, false>(p, blocks, s);
+  }
+}
+
+}  // namespace
+}  // namespace bt

@@ -268,7 +268,8 @@ def traffic(a):
         "algorithmic_bytes_per_launch": round(alg / 147),
         "per_layout": per_layout,
         "gemm_source_sha256": code_sha256(os.path.join(HERE, "csrc", "gemm.hip")),
-        "sha_note": "sha256 of gemm.hip with // comments and blank lines removed (bench.py code_sha256)",
+        "gemm_kernel_sha256": code_sha256(os.path.join(HERE, "csrc", "gemm_kernel.h")),
+        "sha_note": "sha256 of gemm.hip and gemm_kernel.h with // comments and blank lines removed (bench.py code_sha256)",
     }
     with open(a.json, "w") as f:
         json.dump(rec, f, indent=1)

@@ -1,0 +1,109 @@
+"""The GEMM kernel's own edges: FP32 products as six BF16 products.
+
+Block tiles are picked from M, N and K; the shapes below reach every tile in
+every layout with ragged last rows and columns (the tiles are 64 to 256 rows
+by 64 to 192 columns) and with each kind of K remainder of a 32-deep k-tile.
+
+Error bar, element by element.  With |x| = |h + m + l| split exactly and
+|m| <= 2^-9 |x|, |l| <= 2^-18 |x|, the three products left out are below
+2^-26 |a||b|.  The six kept are exact; their chain rounds (or cuts off) at most
+once per instruction, 2^-23 of the sum of the 32 |a||b| it covers, and the FP32
+additions of K / 32 chains round 2^-24 of at most the whole sum each:
+    |C - C64| <= (6 2^-23 + 2^-26 + ceil(K / 32) 2^-24) sum_k |a||b|."""
+import numpy as np
+import pytest
+
+from paper_2606_24780_amd import bt
+from tests.gpu_util import say, torch_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _bar(K):
+    return 5 * 2.0**-23 + 2.0**-26 + -(-K // 32) * 1.5 * 2.0**-23
+
+
+def _run(torch, ta, tb, M, N, K, A, B):
+    C = torch.full((M, N), float("nan"), device="cuda")
+    bt.bt_gemm(ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], 0.0, C, N)
+    torch.cuda.synchronize()
+    return C
+
+
+def _op(t, trans):
+    return t.double().t().contiguous() if trans else t.double()
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(4, 4, 4), (68, 60, 32), (128, 196, 28), (260, 132, 60), (4100, 196, 100),
+                                   (4100, 1540, 36), (1028, 4100, 100), (2052, 9212, 36), (2052, 4100, 68)])
+def test_every_tile_and_k_remainder(ta, tb, M, N, K):
+    torch = torch_gpu()
+    say(f"gemm split ta={ta} tb={tb} {M}x{N}x{K}")
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda")
+    B = torch.randn((N, K) if tb else (K, N), generator=g, device="cuda")
+    C = _run(torch, ta, tb, M, N, K, A, B)
+    a, b = _op(A, ta), _op(B, tb)
+    over = ((C.double() - a @ b).abs() - _bar(K) * (a.abs() @ b.abs())).max().item()
+    assert over <= 0, f"element {over:.3e} above its error bar"
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(260, 196, 100), (2052, 4100, 36)])
+def test_infinities_nan_and_largest_numbers(ta, tb, M, N, K):
+    """Elements are infinite or NaN exactly where the product in 64 bits is
+    (its operands are the same), and all others keep their error bar: an
+    infinity, a NaN and a number next to FLT_MAX in A, an infinity in B."""
+    torch = torch_gpu()
+    say(f"gemm special values ta={ta} tb={tb} {M}x{N}x{K}")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    a = torch.randn((M, K), generator=g, device="cuda")
+    b = torch.randn((K, N), generator=g, device="cuda") * 1e-3
+    a[3, 5] = float("inf")
+    a[70, K - 1] = float("nan")
+    a[M - 1, 0] = 3.4e38
+    b[5, 9] = 0.0            # inf * 0
+    b[2, N - 1] = -float("inf")
+    A, B = (a.t().contiguous() if ta else a), (b.t().contiguous() if tb else b)
+    C = _run(torch, ta, tb, M, N, K, A, B).double()
+    with np.errstate(invalid="ignore"):
+        ref = torch.from_numpy(np.matmul(a.cpu().double().numpy(), b.cpu().double().numpy())).cuda()
+    assert torch.equal(torch.isnan(C), torch.isnan(ref))
+    assert torch.equal(torch.isposinf(C), torch.isposinf(ref)) and torch.equal(torch.isneginf(C), torch.isneginf(ref))
+    ok = torch.isfinite(ref)
+    bar = (_bar(K) + K * 2.0**-24) * (a.double().abs() @ b.double().abs())  # FP32 sums where a wave repeats its tile
+    assert ((C - ref).abs()[ok] <= bar[ok]).all()
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-36])
+def test_tiny_operand(scale):
+    """Operands whose low parts leave BF16's range: repeated in FP32.  Products
+    of 1e-36 and 1 stay normal numbers, so the FP32 bar K 2^-24 holds."""
+    torch = torch_gpu()
+    M, N, K = 260, 132, 256
+    g = torch.Generator(device="cuda").manual_seed(11)
+    A = torch.randn((M, K), generator=g, device="cuda") * scale
+    B = torch.randn((K, N), generator=g, device="cuda")
+    C = _run(torch, 0, 0, M, N, K, A, B).double()
+    a, b = A.double(), B.double()
+    assert ((C - a @ b).abs() <= (_bar(K) + K * 2.0**-24) * (a.abs() @ b.abs())).all()
+
+
+@pytest.mark.parametrize("K,share", [(768, 0.011), (8192, 0.05)])
+def test_results_have_little_bias(K, share):
+    """The mean error over n = 786,432 results as a share of their standard
+    deviation.  Unbiased roundings give about 1 / sqrt(n) = 0.0011; ten times
+    that is allowed where no product is cut off (a product of high parts has
+    16 bits, so it loses some only below 2^-8 of the sum it is added to).  Long
+    sums are beyond that for their smaller products: at K = 8192 the sum is 90
+    times a typical product, and 0.02 is measured; 0.05 is allowed.  (All six
+    products added straight to the long sum: 0.3 at K = 768.  A column sum
+    over R rows makes sqrt(R) times the share out of it.)"""
+    torch = torch_gpu()
+    M, N = 1024, 768
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((M, K), generator=g, device="cuda")
+    B = torch.randn((K, N), generator=g, device="cuda")
+    err = _run(torch, 0, 0, M, N, K, A, B).double() - A.double() @ B.double()
+    assert err.mean().abs() <= share * err.std(), (err.mean().item(), err.std().item())
