@@ -1,6 +1,6 @@
 // Causal multi-head attention, forward and backward, FP32 on the CDNA4
-// matrix cores (v_mfma_f32_32x32x2_f32), tiled with an online softmax so the
-// T x T score matrix never reaches HBM.
+// matrix cores (each product as six BF16 products, bt_internal.h), tiled with
+// an online softmax so the T x T score matrix never reaches HBM.
 //
 // Problem (GPT-2 architecture figure: masked multi-head self-attention;
 // appendix "Attention Forward/Backward", causal case): per batch b and head h,
@@ -17,10 +17,23 @@
 //  * a block = 4 waves = 128 query rows (forward, dQ) or 128 key rows (dK/dV);
 //    each wave owns 32 rows and keeps its row operand (Q, or K and V) in
 //    registers; the streamed operand tiles of 32 rows are double-buffered in
-//    LDS and shared by the 4 waves.  The forward at head dim 64 with full key
-//    tiles copies its key and value tiles straight into swizzled LDS tiles
-//    (global_load_lds_dwordx4, scalar tile base); elsewhere tiles are staged
-//    through registers into padded LDS tiles.
+//    LDS and shared by the 4 waves.
+//  * all products are six BF16 products of exact three-part splits, on
+//    32x32x16 MFMAs (their accumulators lie as those of the FP32 instruction,
+//    so the softmax below is the same for both).  A streamed tile is split once
+//    per block on its way into LDS, as rows (operand of S and dP) and/or as
+//    columns (of O, dV, dK, dQ), stored as the MFMA reads it.  Rows past T and
+//    columns past hd read as 0 from the buffer resource: no masks on the loads.
+//  * a block with a result that is not finite, or with nothing but results
+//    below 2^-96, repeats its pass with the FP32 instructions; token strides
+//    from 2^24 floats on (beyond the buffer offsets) always take that pass.
+//  * what bounds it: two waves per SIMD in dependent phases.  At B = 16,
+//    T = 1024, 12 heads of 64 the forward runs in 190 us (FP32 instructions:
+//    284), the matrix pipe busy in 45% of the cycles and 20% of the wave cycles
+//    spent waiting; dK 317 + dV 204 us (558 in one kernel), 41% and 23%.
+//  * dK and dV are two launches above head dim 32, although each recomputes
+//    the scores: in one kernel their accumulators and split operands leave one
+//    wave per SIMD with copies between VGPRs and AGPRs, 570-620 us.
 //  * products are computed transposed where that makes the next product's
 //    operand a register the lane already holds: S^T = K Q^T leaves each lane
 //    with one query's 16 scores, so the softmax row statistics are in-lane plus
@@ -29,7 +42,7 @@
 //  * exp is computed as exp2 with log2(e)/sqrt(hd) folded into the register
 //    operand.
 //  * backward is deterministic (no atomics).  With the full workspace:
-//    D = rowsum(dO o O) in a small kernel, then one key-major kernel
+//    D = rowsum(dO o O) in a small kernel, then the key-major kernel
 //    recomputes P from lse, accumulates dK and dV and also writes dS / sqrt(hd)
 //    to the workspace (B H T T floats), and dQ = dS K is one batched product
 //    on the GEMM kernel (causal: each 128-row tile sums only keys below its
@@ -39,8 +52,7 @@
 //  * causal blocks above the diagonal are skipped per wave; blocks are
 //    launched heaviest first.
 //  * head dims up to 128 (multiple of 4), zero-padded to 32, 64 or 128
-//    inside the kernels; at 128 the key-major backward keeps its dK/dV
-//    accumulators partly in AGPRs at one wave per SIMD.
+//    inside the kernels.
 //
 // Context parallelism (section "Context Parallelism"): the same kernels, in
 // their SEG instantiation, compute one rank's share of ring attention.  The
@@ -291,71 +303,383 @@ __device__ __forceinline__ void store_T_tile_merge(float* __restrict__ stage, fl
   }
 }
 
-// ---------------------------------------------------- direct-to-LDS tiles
-// The forward's key and value tiles at head dim 64 when every key tile is
-// full: unpadded [32][64] tiles copied straight from global memory into LDS
-// (global_load_lds_dwordx4: a wave instruction moves 1 KB = 4 rows, lane i
-// landing at byte 16 i; a tile is 8 such slices, 2 per wave).  No staging
-// registers, no LDS stores, and every address is a scalar tile base plus a
-// per-lane offset fixed for the whole kernel.  The source of each lane is
-// chosen so the tiles are stored swizzled instead of padded:
-//  * keys (read as float4 along d by 32 consecutive rows): the 16-byte chunk
-//    c of row r is stored at chunk c ^ (r & 15), so the 16 rows a quarter
-//    wave reads land on 16 different bank groups;
-//  * values (read as b32 by 32 consecutive columns, the two lane halves 4
-//    rows apart): rows with bit 2 set have their two 32-column halves
-//    swapped, so the two halves of a wave read different banks.
-__device__ __forceinline__ void fwd_copy_offsets(unsigned (&ok)[2], unsigned (&ov)[2], long long ks, int wave,
-                                                 int lane) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = 4 * (2 * wave + j) + lane / 16;
-    const int c4 = 4 * (lane % 16);  // LDS column of this lane's 16 bytes
-    ok[j] = (unsigned)((row * ks + 4 * ((c4 / 4) ^ (row & 15))) * 4);
-    ov[j] = (unsigned)((row * ks + (c4 ^ (((row >> 2) & 1) << 5))) * 4);
-  }
-}
+// ------------------------------------------- split products (BF16 MFMA)
+// The same products with every FP32 operand as the sum of three BF16 parts
+// (bt_internal.h) on v_mfma_f32_32x32x16_bf16, whose accumulators lie as those
+// of the FP32 instruction.  A streamed 32-row tile X is split once per block
+// on its way into LDS and stored as the MFMAs read it: per part and 16-deep
+// step one KB, lane l's 8 values at 16 l (reads are linear, conflict-free).
+//  * rows form, step c: lane (lr, hh) holds row lr, d = 16 c + 8 hh .. + 7;
+//  * cols form, step (db, s): lane (lr, hh) holds column d = 32 db + lr, rows
+//    16 s + 8 (j / 4) + 4 hh + j % 4 (j < 8): the rows whose probabilities the
+//    lane holds in accumulator registers 8 s .. 8 s + 7.
+// A tile form is 32 HDP values: SU chunks of 8 per thread (half the threads
+// at HDP = 32).
+template <int HDP>
+struct FragForm {
+  static constexpr int STEPS = HDP / 16;
+  static constexpr int PART = 1024 * STEPS;  // bytes of one part
+  static constexpr int BYTES = 3 * PART;
+  static constexpr int SU = HDP > 64 ? HDP / 64 : 1;
+  static constexpr int ACTIVE = HDP < 64 ? 4 * HDP : 256;  // threads with a chunk
+};
 
-// S = (rows of the swizzled key tile) x (register operand), as
-// mma_rows_by_reg<64, ...> on an unpadded tile.
-__device__ __forceinline__ void mma_rows_by_reg_swz(floatx16& acc, const float* __restrict__ s,
-                                                    const float (&f)[32], int lr, int hh) {
+// Loads of one form of a streamed matrix (token stride `stride` floats, below
+// 2^24): a uniform buffer resource per tile, limited to its rows below T, and
+// per-lane byte offsets fixed for the whole pass.  Rows past T and columns
+// past hd (offset FAR) lie outside the resource and read as 0.
+constexpr unsigned FAR = 0x80000000u;
+constexpr long long FORM_STRIDE = 1LL << 24;  // wider token strides take the FP32 pass
+template <int HDP, bool COLS>
+struct FormLoad {
+  static constexpr int SU = FragForm<HDP>::SU;
+  unsigned off[SU][COLS ? 1 : 2];
+  int stride4;
+  __device__ __forceinline__ FormLoad(long long stride, int hd, int tid) : stride4(4 * (int)stride) {
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const floatx4 a = *reinterpret_cast<const floatx4*>(s + lr * 64 + 4 * ((8 * hh + c) ^ (lr & 15)));
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc = mfma32(a[q], f[4 * c + q], acc);
-  }
-}
-
-// out^T += (swizzled value tile)^T x w, as mma_tile_T_by_acc<64, ...>:
-// register st of lane half hh holds row acc_row(st, hh), whose bit 2 is hh.
-__device__ __forceinline__ void mma_tile_T_by_acc_swz(floatx16 (&out)[2], const float* __restrict__ s,
-                                                      const floatx16& w, int lr, int hh) {
-#pragma unroll
-  for (int db = 0; db < 2; ++db)
-#pragma unroll
-    for (int st = 0; st < 16; ++st) {
-      const float a = s[acc_row(st, hh) * 64 + ((32 * db + lr) ^ (hh << 5))];
-      out[db] = mfma32(a, w[st], out[db]);
+    for (int i = 0; i < SU; ++i) {
+      const int u = tid + 256 * i, c = u >> 6, lr = u & 31, hh = (u >> 5) & 1;
+      if (COLS) {
+        const int d = 32 * (c >> 1) + lr;
+        off[i][0] = d < hd ? (unsigned)((16 * (c & 1) + 4 * hh) * stride4 + 4 * d) : FAR;
+      } else {
+        const int d = 16 * c + 8 * hh;
+        off[i][0] = d < hd ? (unsigned)(lr * stride4 + 4 * d) : FAR;
+        off[i][COLS ? 0 : 1] = d + 4 < hd ? (unsigned)(lr * stride4 + 4 * d + 16) : FAR;
+      }
     }
+  }
+  // The tile of `rows` valid rows (at most 32) that starts at src.
+  __device__ __forceinline__ void load(float (&r)[SU][8], const float* src, int rows, int tid) const {
+    if (FragForm<HDP>::ACTIVE < 256 && tid >= FragForm<HDP>::ACTIVE) return;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), (short)0, stride4 * min(rows, 32),
+                                                        0x00020000);
+#pragma unroll
+    for (int i = 0; i < SU; ++i) {
+      if (COLS) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          r[i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                  rsrc, off[i][0], (8 * (j >> 2) + (j & 3)) * stride4, 0));
+      } else {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          const floatx4 x = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i][COLS ? 0 : g], 0, 0));
+#pragma unroll
+          for (int j = 0; j < 4; ++j) r[i][4 * g + j] = x[j];
+        }
+      }
+    }
+  }
+};
+
+template <int HDP>
+__device__ __forceinline__ void store_form(char* __restrict__ dst, const float (&r)[FragForm<HDP>::SU][8], int tid) {
+  if (FragForm<HDP>::ACTIVE < 256 && tid >= FragForm<HDP>::ACTIVE) return;
+#pragma unroll
+  for (int i = 0; i < FragForm<HDP>::SU; ++i) {
+    const Split8 v = split8(r[i]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      *reinterpret_cast<uintx4*>(dst + q * FragForm<HDP>::PART + 16 * (tid + 256 * i)) = v.p[q];
+  }
+}
+
+// Per-lane register operand: row t of src, d = 16 c + 8 hh .. + 7 in step c.
+template <int HDP>
+__device__ __forceinline__ void load_split_operand(Split8 (&f)[HDP / 16], const float* __restrict__ src,
+                                                   long long stride, int t, int T, int hd, int hh, float scale) {
+#pragma unroll
+  for (int c = 0; c < HDP / 16; ++c) {
+    float x[8];
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const int d = 16 * c + 8 * hh + 4 * g;
+      floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (t < T && d < hd) v = *reinterpret_cast<const floatx4*>(src + (long long)t * stride + d);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * g + j] = v[j] * scale;
+    }
+    f[c] = split8(x);
+  }
+}
+
+__device__ __forceinline__ floatx16 mfma32b(const uintx4& a, const uintx4& b, const floatx16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                 0);
+}
+
+// One 16-deep step of a split product: the high parts' product into acc, the
+// other five, smallest first, into small (added to acc by the caller: the
+// matrix instructions would cut them off against a long sum).
+__device__ __forceinline__ void mfma_split32(floatx16& acc, floatx16& small, const char* a, int part, const Split8& b) {
+  const uintx4 h = *reinterpret_cast<const uintx4*>(a);
+  const uintx4 m = *reinterpret_cast<const uintx4*>(a + part);
+  const uintx4 l = *reinterpret_cast<const uintx4*>(a + 2 * part);
+  small = mfma32b(l, b.p[0], small);
+  small = mfma32b(h, b.p[2], small);
+  small = mfma32b(m, b.p[1], small);
+  small = mfma32b(m, b.p[0], small);
+  small = mfma32b(h, b.p[1], small);
+  acc = mfma32b(h, b.p[0], acc);
+}
+
+// acc = X f^T over d: X a tile in rows form, f the lane's register operand.
+// The small products start the chain that the high parts' continue: over at
+// most 128 terms nothing is cut off that counts (2^-27 of the sum, once).
+template <int HDP>
+__device__ __forceinline__ void split_rows_by_reg(floatx16& acc, const char* __restrict__ x,
+                                                  const Split8 (&f)[HDP / 16], int lane) {
+  constexpr int PART = FragForm<HDP>::PART;
+  uintx4 h[HDP / 16];
+  zero16(acc);
+#pragma unroll
+  for (int c = 0; c < HDP / 16; ++c) {
+    const char* a = x + 1024 * c + 16 * lane;
+    h[c] = *reinterpret_cast<const uintx4*>(a);
+    const uintx4 m = *reinterpret_cast<const uintx4*>(a + PART);
+    const uintx4 l = *reinterpret_cast<const uintx4*>(a + 2 * PART);
+    acc = mfma32b(l, f[c].p[0], acc);
+    acc = mfma32b(h[c], f[c].p[2], acc);
+    acc = mfma32b(m, f[c].p[1], acc);
+    acc = mfma32b(m, f[c].p[0], acc);
+    acc = mfma32b(h[c], f[c].p[1], acc);
+  }
+#pragma unroll
+  for (int c = 0; c < HDP / 16; ++c) acc = mfma32b(h[c], f[c].p[0], acc);
+}
+
+// out^T[d][col] += sum_row X[row][d] W[row][col]: X a tile in cols form, W
+// (32 x 32) in accumulator layout.  `out` and `small` together hold the sum:
+// the small products would be cut off against the long one.  Where the
+// registers allow it `small` lasts over all tiles; null: added tile by tile
+// (a vector instruction per element, three where accumulators are in AGPRs).
+template <int HDP>
+__device__ __forceinline__ void split_tile_T_by_acc(floatx16 (&out)[HDP / 32], floatx16 (*small)[HDP / 32],
+                                                    const char* __restrict__ x, const floatx16& w, int lane) {
+  Split8 f[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = w[8 * s + j];
+    f[s] = split8(v);
+  }
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) {
+    floatx16 sum;
+    if (small) sum = (*small)[db];
+    else zero16(sum);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      mfma_split32(out[db], sum, x + 1024 * (2 * db + s) + 16 * lane, FragForm<HDP>::PART, f[s]);
+    if (small) (*small)[db] = sum;
+    else out[db] += sum;
+  }
+}
+
+// Whether a wave's results have to be computed again in FP32: one is not
+// finite (parts of an infinity, or of a number near FLT_MAX, are NaN), or all
+// are so small that low parts may have left BF16's range.
+constexpr float TINY_RESULT = 0x1p-96f;
+template <int N>
+__device__ __forceinline__ bool needs_f32(const floatx16 (&o)[N], float more) {
+  float mx = __builtin_fabsf(more);
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = __builtin_elementwise_maximum(mx, __builtin_fabsf(o[i][r]));
+  return __any(!(mx <= 0x1.fffffep127f)) || (!__any(mx >= TINY_RESULT) && __any(mx > 0.f));
 }
 
 // ---------------------------------------------------------------- forward
-// SEG: one rank's share (keys from sg.kv, visibility by segment positions,
-// optional merge into the running out/lse).
-template <int HDP, bool SEG, bool DTL = false>
-__global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const float* __restrict__ qkv,
-                                                          float* __restrict__ out,
-                                                          float* __restrict__ lse, AttnShape sh,
-                                                          AttnSegs sg) {
+// The streamed key range of one block of 128 queries, shared by the passes
+// below: causal, a prefix of the rows; SEG, a prefix of each key segment (n0
+// tiles of the first).
+template <bool SEG>
+struct KeyTiles {
+  int nkb, n0;
+  const AttnSegs& sg;
+  __device__ KeyTiles(int q0, int qp0, int T, int Tk, const AttnSegs& s) : sg(s) {
+    if (SEG) {
+      n0 = seg_prefix_tiles(qp0 + 127, sg.k_pos[0], sg.seg);
+      nkb = n0 + (Tk > sg.seg ? seg_prefix_tiles(qp0 + 127, sg.k_pos[1], sg.seg) : 0);
+    } else {
+      nkb = min(T - 1, q0 + 127) / 32 + 1;
+      n0 = nkb;
+    }
+  }
+  __device__ int row(int kb) const { return SEG ? (kb < n0 ? 32 * kb : sg.seg + 32 * (kb - n0)) : 32 * kb; }
+  __device__ int pos(int kb) const {
+    return SEG ? (kb < n0 ? sg.k_pos[0] + 32 * kb : sg.k_pos[1] + 32 * (kb - n0)) : 32 * kb;
+  }
+};
+
+// Masks a 32 x 32 block of scores S^T[key][query] (uniform: diagonal or ragged).
+// The empty asm keeps the compiler from turning the caller's branch into 48
+// selects on every tile.
+__device__ __forceinline__ void mask_scores(floatx16& s, int kp0, int my_qpos, int kr0, int Tk, int hh) {
+  asm volatile("");
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int kk = acc_row(r, hh);
+    const bool dead = (kp0 + kk > my_qpos) | (kr0 + kk >= Tk);
+    s[r] = dead ? -INFINITY : s[r];
+  }
+}
+
+// Online softmax over all key tiles of a wave's 32 queries, split products.
+// What bounds it: per 32 x 32 tile at head dim 64 a wave issues 48 MFMAs (1536
+// cycles) and about 330 vector instructions (1320): the conversions of the
+// probabilities, the exponentials and its share of the tiles' conversions.
+// The running maximum therefore moves only when a score exceeds it by more
+// than 2^8 (after the first tile hardly ever): probabilities stay below 2^8,
+// and the accumulators are not rescaled tile by tile.
+template <int HDP, bool SEG>
+__device__ __forceinline__ void fwd_pass_split(floatx16 (&o)[HDP / 32], float& m_run, float& l_run, char* smem,
+                                               const float* qbase, long long rs, const float* kbase, long long ks,
+                                               int C, int T, int Tk, int hd, float qscale, int my_q, int wpos,
+                                               const KeyTiles<SEG>& kt, int tid) {
+  using F = FragForm<HDP>;
+  constexpr int BUF = 2 * F::BYTES;
+  const int lane = tid & 63, lr = lane & 31, hh = lane >> 5;
+  const float* vbase = kbase + C;
+  Split8 qf[HDP / 16];
+  load_split_operand<HDP>(qf, qbase, rs, my_q, T, hd, hh, qscale);
+  floatx16 o_small[HDP / 32];
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) {
+    zero16(o[db]);
+    zero16(o_small[db]);
+  }
+  m_run = -INFINITY;
+  l_run = 0.f;
+
+  float rk[F::SU][8], rv[F::SU][8];
+  const FormLoad<HDP, false> lk(ks, hd, tid);
+  const FormLoad<HDP, true> lv(ks, hd, tid);
+  auto load = [&](int kb) {
+    const long long r0 = kt.row(kb);
+    lk.load(rk, kbase + r0 * ks, Tk - (int)r0, tid);
+    lv.load(rv, vbase + r0 * ks, Tk - (int)r0, tid);
+  };
+  auto store = [&](char* buf) {
+    store_form<HDP>(buf, rk, tid);
+    store_form<HDP>(buf + F::BYTES, rv, tid);
+  };
+  if (kt.nkb > 0) {
+    load(0);
+    store(smem);
+  }
+  __syncthreads();
+  for (int kb = 0; kb < kt.nkb; ++kb) {
+    const char* cur = smem + (kb & 1) * BUF;
+    const bool more = kb + 1 < kt.nkb;
+    if (more) load(kb + 1);
+    const int kp0 = kt.pos(kb);
+    if (kp0 <= wpos + 31) {  // some key of the tile visible to this wave
+      floatx16 s;
+      split_rows_by_reg<HDP>(s, cur, qf, lane);
+      const int kr0 = kt.row(kb);
+      if ((kp0 + 31 > wpos) || (kr0 + 32 > Tk)) mask_scores(s, kp0, wpos + lr, kr0, Tk, hh);
+      float bmax = s[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) bmax = fmaxf(bmax, s[r]);
+      if (__any(bmax > m_run + 8.f)) {
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+        const float m_new = fmaxf(m_run, bmax);
+        const float alpha = exp2_hw(m_run - m_new);
+        l_run *= alpha;
+        m_run = m_new;
+#pragma unroll
+        for (int db = 0; db < HDP / 32; ++db) {
+          o[db] *= alpha;
+          o_small[db] *= alpha;
+        }
+      }
+      float psum = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] = exp2_hw(s[r] - m_run);
+        psum += s[r];
+      }
+      l_run += psum;
+      split_tile_T_by_acc<HDP>(o, &o_small, cur + F::BYTES, s, lane);
+    }
+    if (more) store(smem + ((kb + 1) & 1) * BUF);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) o[db] += o_small[db];
+}
+
+// The same with the FP32 matrix instructions, for inputs the parts cannot
+// represent.
+template <int HDP, bool SEG>
+__device__ __forceinline__ void fwd_pass_f32(floatx16 (&o)[HDP / 32], float& m_run, float& l_run, float* smem,
+                                          const float* qbase, long long rs, const float* kbase, long long ks, int C,
+                                          int T, int Tk, int hd, float qscale, int my_q, int wpos,
+                                          const KeyTiles<SEG>& kt, int tid) {
   constexpr int LDK = HDP + 4;   // float4-read tiles
   constexpr int LDV = HDP + 8;   // b32-read tiles (halves 4 rows apart -> other banks)
-  constexpr int KSZ = 32 * LDK, VSZ = 32 * LDV;
-  __shared__ __attribute__((aligned(16))) float smem[2 * (KSZ + VSZ)];
-  static_assert(4 * 32 * (HDP + 4) + 4 * 32 <= 2 * (KSZ + VSZ), "epilogue staging must fit");
+  constexpr int KSZ = 32 * LDK;
+  const int lane = tid & 63, lr = lane & 31, hh = lane >> 5;
+  const float* vbase = kbase + C;
+  float qf[HDP / 2];
+  load_reg_operand<HDP>(qf, qbase, rs, my_q, T, hd, hh, qscale);
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) zero16(o[db]);
+  m_run = -INFINITY;
+  l_run = 0.f;
+  for (int kb = 0; kb < kt.nkb; ++kb) {
+    floatx4 rk[HDP / 32], rv[HDP / 32];
+    load_rows_clamped<HDP>(rk, kbase, ks, kt.row(kb), Tk, hd, tid);
+    load_rows_clamped<HDP>(rv, vbase, ks, kt.row(kb), Tk, hd, tid);
+    __syncthreads();
+    store_rows_masked<HDP, LDK>(smem, rk, tid, kt.row(kb), Tk, hd);
+    store_rows_masked<HDP, LDV>(smem + KSZ, rv, tid, kt.row(kb), Tk, hd);
+    __syncthreads();
+    const int kp0 = kt.pos(kb);
+    if (kp0 > wpos + 31) continue;
+    floatx16 s;
+    zero16(s);
+    mma_rows_by_reg<HDP, LDK>(s, smem, qf, lr, hh);
+    const int kr0 = kt.row(kb);
+    if ((kp0 + 31 > wpos) || (kr0 + 32 > Tk)) mask_scores(s, kp0, wpos + lr, kr0, Tk, hh);
+    float bmax = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, s[r]);
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+    const float m_new = fmaxf(m_run, bmax);
+    const float alpha = exp2_hw(m_run - m_new);
+    float psum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = exp2_hw(s[r] - m_new);
+      psum += s[r];
+    }
+    l_run = l_run * alpha + psum;
+    m_run = m_new;
+#pragma unroll
+    for (int db = 0; db < HDP / 32; ++db) o[db] *= alpha;
+    mma_tile_T_by_acc<HDP, LDV>(o, smem + KSZ, s, lr, hh);
+  }
+  __syncthreads();
+}
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// SEG: one rank's share (keys from sg.kv, visibility by segment positions,
+// optional merge into the running out/lse).
+template <int HDP, bool SEG>
+__global__ void __launch_bounds__(256, HDP <= 64 ? 2 : 1) attn_fwd_kernel(const float* __restrict__ qkv,
+                                                                          float* __restrict__ out,
+                                                                          float* __restrict__ lse, AttnShape sh,
+                                                                          AttnSegs sg) {
+  constexpr int SMEM = 4 * FragForm<HDP>::BYTES;
+  __shared__ __attribute__((aligned(16))) char smem[SMEM];
+  static_assert(4 * (4 * 32 * (HDP + 4) + 4 * 32) <= SMEM, "epilogue staging must fit");
+  static_assert(4 * 32 * (2 * HDP + 12) <= SMEM, "FP32 tiles must fit");
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, hh = lane >> 5;
   const int BH = sh.B * sh.H;
   const int nqt = (sh.T + 127) / 128;
@@ -368,7 +692,6 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const float* __restric
   const long long ks = SEG ? sg.kv_stride : rs;
   const float* qbase = qkv + (long long)b * sh.T * rs + (long long)h * sh.hd;
   const float* kbase = SEG ? sg.kv + (long long)b * Tk * ks + (long long)h * sh.hd : qbase + C;
-  const float* vbase = kbase + C;
 
   const int q0 = qt * 128;
   const int qw0 = q0 + 32 * wave;
@@ -376,119 +699,18 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const float* __restric
   // positions: the block's 128 rows lie in one segment
   const int qp0 = SEG ? seg_pos(sg.q_pos, sg.seg, q0) : q0;
   const int wpos = qp0 + 32 * wave;  // this wave's first query position
-  const int my_qpos = wpos + lr;
   const float qscale = LOG2E / sqrtf((float)sh.hd);
-
-  float qf[HDP / 2];
-  load_reg_operand<HDP>(qf, qbase, rs, my_q, sh.T, sh.hd, hh, qscale);
+  const KeyTiles<SEG> kt(q0, qp0, sh.T, Tk, sg);
 
   floatx16 o[HDP / 32];
-#pragma unroll
-  for (int db = 0; db < HDP / 32; ++db) zero16(o[db]);
-  float m_run = -INFINITY, l_run = 0.f;
-
-  // streamed key tiles: causal, a prefix of the rows; SEG, a prefix of each
-  // key segment (n0 tiles of the first)
-  int nkb, n0;
-  if (SEG) {
-    n0 = seg_prefix_tiles(qp0 + 127, sg.k_pos[0], sg.seg);
-    nkb = n0 + (Tk > sg.seg ? seg_prefix_tiles(qp0 + 127, sg.k_pos[1], sg.seg) : 0);
-  } else {
-    nkb = min(sh.T - 1, q0 + 127) / 32 + 1;
-    n0 = nkb;
-  }
-  auto key_row = [&](int kb) { return SEG ? (kb < n0 ? 32 * kb : sg.seg + 32 * (kb - n0)) : 32 * kb; };
-  auto key_pos = [&](int kb) { return SEG ? (kb < n0 ? sg.k_pos[0] + 32 * kb : sg.k_pos[1] + 32 * (kb - n0)) : 32 * kb; };
-
-  floatx4 rk[HDP / 32], rv[HDP / 32];
-  // DTL: key and value tiles copied straight into LDS (below)
-  unsigned ok_[2], ov_[2];
-  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)smem;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  if constexpr (DTL) fwd_copy_offsets(ok_, ov_, ks, wave_u, lane);
-  auto issue = [&](int kb, int buf) {
-    const long long r0 = key_row(kb);
-    const unsigned l = lds0 + 4u * buf * (KSZ + VSZ) + 2048u * wave_u;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) copy16_to_lds_sbase(kbase + r0 * ks, ok_[j], l + 1024u * j);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) copy16_to_lds_sbase(vbase + r0 * ks, ov_[j], l + 4u * KSZ + 1024u * j);
-  };
-  if (nkb > 0) {
-    if constexpr (DTL) {
-      issue(0, 0);
-      wait_copies();
-    } else {
-      load_rows_clamped<HDP>(rk, kbase, ks, key_row(0), Tk, sh.hd, tid);
-      load_rows_clamped<HDP>(rv, vbase, ks, key_row(0), Tk, sh.hd, tid);
-      store_rows_masked<HDP, LDK>(smem, rk, tid, key_row(0), Tk, sh.hd);
-      store_rows_masked<HDP, LDV>(smem + KSZ, rv, tid, key_row(0), Tk, sh.hd);
-    }
-  }
-  __syncthreads();
-
-  for (int kb = 0; kb < nkb; ++kb) {
-    const int cur = kb & 1;
-    const bool more = kb + 1 < nkb;
-    if (more) {
-      if constexpr (DTL) {
-        issue(kb + 1, cur ^ 1);  // the other buffer was last read before the previous barrier
-      } else {
-        load_rows_clamped<HDP>(rk, kbase, ks, key_row(kb + 1), Tk, sh.hd, tid);
-        load_rows_clamped<HDP>(rv, vbase, ks, key_row(kb + 1), Tk, sh.hd, tid);
-      }
-    }
-    const int kp0 = key_pos(kb);
-    if (kp0 <= wpos + 31) {  // some key of the tile visible to this wave
-      const float* sK = smem + cur * (KSZ + VSZ);
-      const float* sV = sK + KSZ;
-      floatx16 s;
-      zero16(s);
-      if constexpr (DTL)
-        mma_rows_by_reg_swz(s, sK, qf, lr, hh);
-      else
-        mma_rows_by_reg<HDP, LDK>(s, sK, qf, lr, hh);
-      const int kr0 = key_row(kb);
-      if ((kp0 + 31 > wpos) || (kr0 + 32 > Tk)) {  // diagonal or ragged tile (uniform)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kk = acc_row(r, hh);
-          const bool dead = (kp0 + kk > my_qpos) | (kr0 + kk >= Tk);
-          s[r] = dead ? -INFINITY : s[r];
-        }
-      }
-      float bmax = -INFINITY;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, s[r]);
-      bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-      const float m_new = fmaxf(m_run, bmax);
-      const float alpha = exp2_hw(m_run - m_new);
-      float psum = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = exp2_hw(s[r] - m_new);
-        psum += s[r];
-      }
-      l_run = l_run * alpha + psum;
-      m_run = m_new;
-#pragma unroll
-      for (int db = 0; db < HDP / 32; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-      if constexpr (DTL)
-        mma_tile_T_by_acc_swz(o, sV, s, lr, hh);
-      else
-        mma_tile_T_by_acc<HDP, LDV>(o, sV, s, lr, hh);
-    }
-    if constexpr (DTL) {
-      wait_copies();
-    } else if (more) {
-      float* sN = smem + (cur ^ 1) * (KSZ + VSZ);
-      store_rows_masked<HDP, LDK>(sN, rk, tid, key_row(kb + 1), Tk, sh.hd);
-      store_rows_masked<HDP, LDV>(sN + KSZ, rv, tid, key_row(kb + 1), Tk, sh.hd);
-    }
-    __syncthreads();
-  }
+  float m_run, l_run;
+  const bool fits = ks < FORM_STRIDE;
+  if (fits)
+    fwd_pass_split<HDP, SEG>(o, m_run, l_run, smem, qbase, rs, kbase, ks, C, sh.T, Tk, sh.hd, qscale, my_q, wpos, kt,
+                           tid);
+  if (__builtin_expect(!fits || __syncthreads_or(needs_f32(o, l_run)), 0))
+    fwd_pass_f32<HDP, SEG>(o, m_run, l_run, reinterpret_cast<float*>(smem), qbase, rs, kbase, ks, C, sh.T, Tk, sh.hd,
+                           qscale, my_q, wpos, kt, tid);
 
   // A query that saw no key (possible only across shards) keeps l = 0:
   // output 0, lse -inf.
@@ -496,10 +718,11 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const float* __restric
   const bool seen = l_tot > 0.f;
   const float inv = seen ? 1.f / l_tot : 0.f;
   const float row_lse = seen ? (m_run + log2f(l_tot)) * LN2 : -INFINITY;
-  float* stage = smem + wave * 32 * (HDP + 4);
+  float* const fsm = reinterpret_cast<float*>(smem);
+  float* stage = fsm + wave * 32 * (HDP + 4);
   float* obase = out + (long long)b * sh.T * C + (long long)h * sh.hd;
   if (SEG && (sg.flags & SEG_MERGE)) {
-    float* wts = smem + 4 * 32 * (HDP + 4) + 32 * wave;
+    float* wts = fsm + 4 * 32 * (HDP + 4) + 32 * wave;
     store_T_tile_merge<HDP>(stage, wts, o, inv, row_lse, obase, C, lse + (long long)bh * sh.T, qw0, sh.T,
                             sh.hd, lane);
   } else {
@@ -512,17 +735,121 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const float* __restric
 // Causal: computes D = rowsum(dO o O) for its rows and stores it to Dws for
 // the key-major kernel.  SEG: reads D from Dws (the final output's row sums,
 // computed once per rank), keys from sg.kv, optional dQ accumulation.
+
+// dS^T from the scores and dP^T of one 32 x 32 block, in place of the scores.
+__device__ __forceinline__ void dq_scores(floatx16& s, const floatx16& dp, float lse2, float Dq, bool masked, int kp0,
+                                          int my_qpos, int kr0, int Tk, int hh) {
+  if (masked) {  // diagonal or ragged tile (uniform)
+    asm volatile("");  // a branch, not selects
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int kk = acc_row(r, hh);
+      const bool dead = (kp0 + kk > my_qpos) | (kr0 + kk >= Tk);
+      const float p = dead ? 0.f : exp2_hw(s[r] - lse2);
+      s[r] = p * (dp[r] - Dq);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = exp2_hw(s[r] - lse2) * (dp[r] - Dq);
+  }
+}
+
+template <int HDP, bool SEG>
+__device__ __forceinline__ void dq_pass_split(floatx16 (&dq)[HDP / 32], char* smem, const float* qbase, long long rs,
+                                              const float* dobase, const float* kbase, long long ks, int C, int T,
+                                              int Tk, int hd, float sm_scale, float lse2, float Dq, int my_q, int wpos,
+                                              const KeyTiles<SEG>& kt, int tid) {
+  using F = FragForm<HDP>;
+  constexpr int BUF = 3 * F::BYTES;  // K in both forms, V in rows form
+  const int lane = tid & 63, lr = lane & 31, hh = lane >> 5;
+  const float* vbase = kbase + C;
+  Split8 qf[HDP / 16], dof[HDP / 16];
+  load_split_operand<HDP>(qf, qbase, rs, my_q, T, hd, hh, LOG2E * sm_scale);
+  load_split_operand<HDP>(dof, dobase, C, my_q, T, hd, hh, 1.f);
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) zero16(dq[db]);
+
+  float rk[F::SU][8], rkc[F::SU][8], rv[F::SU][8];
+  const FormLoad<HDP, false> lrows(ks, hd, tid);
+  const FormLoad<HDP, true> lcols(ks, hd, tid);
+  auto load = [&](int kb) {
+    const long long r0 = kt.row(kb);
+    lrows.load(rk, kbase + r0 * ks, Tk - (int)r0, tid);
+    lcols.load(rkc, kbase + r0 * ks, Tk - (int)r0, tid);
+    lrows.load(rv, vbase + r0 * ks, Tk - (int)r0, tid);
+  };
+  auto store = [&](char* buf) {
+    store_form<HDP>(buf, rk, tid);
+    store_form<HDP>(buf + F::BYTES, rkc, tid);
+    store_form<HDP>(buf + 2 * F::BYTES, rv, tid);
+  };
+  if (kt.nkb > 0) {
+    load(0);
+    store(smem);
+  }
+  __syncthreads();
+  for (int kb = 0; kb < kt.nkb; ++kb) {
+    const char* cur = smem + (kb & 1) * BUF;
+    const bool more = kb + 1 < kt.nkb;
+    if (more) load(kb + 1);
+    const int kp0 = kt.pos(kb), kr0 = kt.row(kb);
+    if (kp0 <= wpos + 31) {
+      floatx16 s, dp;
+      split_rows_by_reg<HDP>(s, cur, qf, lane);                  // S^T  [key][q]
+      split_rows_by_reg<HDP>(dp, cur + 2 * F::BYTES, dof, lane);  // dP^T [key][q]
+      dq_scores(s, dp, lse2, Dq, (kp0 + 31 > wpos) || (kr0 + 32 > Tk), kp0, wpos + lr, kr0, Tk, hh);
+      split_tile_T_by_acc<HDP>(dq, nullptr, cur + F::BYTES, s, lane);  // dQ^T[d][q] += K^T dS^T
+    }
+    if (more) store(smem + ((kb + 1) & 1) * BUF);
+    __syncthreads();
+  }
+}
+
+template <int HDP, bool SEG>
+__device__ __forceinline__ void dq_pass_f32(floatx16 (&dq)[HDP / 32], float* smem, const float* qbase, long long rs,
+                                            const float* dobase, const float* kbase, long long ks, int C, int T,
+                                            int Tk, int hd, float sm_scale, float lse2, float Dq, int my_q, int wpos,
+                                            const KeyTiles<SEG>& kt, int tid) {
+  constexpr int LD = HDP + 4;  // K: read as float4 (S) and as b32 (dQ); V: as float4 (dP)
+  constexpr int KSZ = 32 * LD;
+  const int lane = tid & 63, lr = lane & 31, hh = lane >> 5;
+  const float* vbase = kbase + C;
+  float qf[HDP / 2], dof[HDP / 2];
+  load_reg_operand<HDP>(qf, qbase, rs, my_q, T, hd, hh, LOG2E * sm_scale);
+  load_reg_operand<HDP>(dof, dobase, C, my_q, T, hd, hh, 1.f);
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) zero16(dq[db]);
+  for (int kb = 0; kb < kt.nkb; ++kb) {
+    floatx4 rk[HDP / 32], rv[HDP / 32];
+    load_rows_clamped<HDP>(rk, kbase, ks, kt.row(kb), Tk, hd, tid);
+    load_rows_clamped<HDP>(rv, vbase, ks, kt.row(kb), Tk, hd, tid);
+    __syncthreads();
+    store_rows_masked<HDP, LD>(smem, rk, tid, kt.row(kb), Tk, hd);
+    store_rows_masked<HDP, LD>(smem + KSZ, rv, tid, kt.row(kb), Tk, hd);
+    __syncthreads();
+    const int kp0 = kt.pos(kb), kr0 = kt.row(kb);
+    if (kp0 > wpos + 31) continue;
+    floatx16 s, dp;
+    zero16(s);
+    zero16(dp);
+    mma_rows_by_reg<HDP, LD>(s, smem, qf, lr, hh);
+    mma_rows_by_reg<HDP, LD>(dp, smem + KSZ, dof, lr, hh);
+    dq_scores(s, dp, lse2, Dq, (kp0 + 31 > wpos) || (kr0 + 32 > Tk), kp0, wpos + lr, kr0, Tk, hh);
+    mma_tile_T_by_acc<HDP, LD>(dq, smem, s, lr, hh);
+  }
+  __syncthreads();
+}
+
 template <int HDP, bool SEG>
 __global__ void __launch_bounds__(256, HDP > 64 ? 1 : 2) attn_bwd_dq_kernel(
     const float* __restrict__ dout, const float* __restrict__ qkv, const float* __restrict__ out,
     const float* __restrict__ lse, float* __restrict__ dqkv, float* __restrict__ Dws, AttnShape sh,
     AttnSegs sg) {
-  constexpr int LDK = HDP + 4;  // K: read as float4 (S) and as b32 (dQ)
-  constexpr int LDV = HDP + 4;  // V: read as float4 (dP)
-  constexpr int KSZ = 32 * LDK, VSZ = 32 * LDV;
-  __shared__ __attribute__((aligned(16))) float smem[2 * (KSZ + VSZ)];
+  constexpr int SMEM = 6 * FragForm<HDP>::BYTES;
+  __shared__ __attribute__((aligned(16))) char smem[SMEM];
+  static_assert(4 * 4 * 32 * (HDP + 4) <= SMEM, "epilogue staging and FP32 tiles must fit");
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, hh = lane >> 5;
   const int BH = sh.B * sh.H;
   const int nqt = (sh.T + 127) / 128;
@@ -535,7 +862,6 @@ __global__ void __launch_bounds__(256, HDP > 64 ? 1 : 2) attn_bwd_dq_kernel(
   const long long ks = SEG ? sg.kv_stride : rs;
   const float* qbase = qkv + (long long)b * sh.T * rs + (long long)h * sh.hd;
   const float* kbase = SEG ? sg.kv + (long long)b * Tk * ks + (long long)h * sh.hd : qbase + C;
-  const float* vbase = kbase + C;
   const float* dobase = dout + (long long)b * sh.T * C + (long long)h * sh.hd;
 
   const int q0 = qt * 128;
@@ -543,18 +869,15 @@ __global__ void __launch_bounds__(256, HDP > 64 ? 1 : 2) attn_bwd_dq_kernel(
   const int my_q = qw0 + lr;
   const int qp0 = SEG ? seg_pos(sg.q_pos, sg.seg, q0) : q0;
   const int wpos = qp0 + 32 * wave;
-  const int my_qpos = wpos + lr;
   const float sm_scale = 1.f / sqrtf((float)sh.hd);
 
-  float qf[HDP / 2], dof[HDP / 2];
-  load_reg_operand<HDP>(qf, qbase, rs, my_q, sh.T, sh.hd, hh, LOG2E * sm_scale);
-  load_reg_operand<HDP>(dof, dobase, C, my_q, sh.T, sh.hd, hh, 1.f);
   float Dq;
   if (SEG) {
     Dq = my_q < sh.T ? Dws[(long long)bh * sh.T + my_q] : 0.f;
   } else {
     const float* obase = out + (long long)b * sh.T * C + (long long)h * sh.hd;
-    float of[HDP / 2];
+    float of[HDP / 2], dof[HDP / 2];
+    load_reg_operand<HDP>(dof, dobase, C, my_q, sh.T, sh.hd, hh, 1.f);
     load_reg_operand<HDP>(of, obase, C, my_q, sh.T, sh.hd, hh, 1.f);
     float part = 0.f;
 #pragma unroll
@@ -563,70 +886,17 @@ __global__ void __launch_bounds__(256, HDP > 64 ? 1 : 2) attn_bwd_dq_kernel(
     if (hh == 0 && my_q < sh.T) Dws[(long long)bh * sh.T + my_q] = Dq;
   }
   const float lse2 = my_q < sh.T ? lse[(long long)bh * sh.T + my_q] * LOG2E : 0.f;
+  const KeyTiles<SEG> kt(q0, qp0, sh.T, Tk, sg);
 
   floatx16 dq[HDP / 32];
-#pragma unroll
-  for (int db = 0; db < HDP / 32; ++db) zero16(dq[db]);
-
-  int nkb, n0;
-  if (SEG) {
-    n0 = seg_prefix_tiles(qp0 + 127, sg.k_pos[0], sg.seg);
-    nkb = n0 + (Tk > sg.seg ? seg_prefix_tiles(qp0 + 127, sg.k_pos[1], sg.seg) : 0);
-  } else {
-    nkb = min(sh.T - 1, q0 + 127) / 32 + 1;
-    n0 = nkb;
-  }
-  auto key_row = [&](int kb) { return SEG ? (kb < n0 ? 32 * kb : sg.seg + 32 * (kb - n0)) : 32 * kb; };
-  auto key_pos = [&](int kb) { return SEG ? (kb < n0 ? sg.k_pos[0] + 32 * kb : sg.k_pos[1] + 32 * (kb - n0)) : 32 * kb; };
-
-  floatx4 rk[HDP / 32], rv[HDP / 32];
-  if (nkb > 0) {
-    load_rows_clamped<HDP>(rk, kbase, ks, key_row(0), Tk, sh.hd, tid);
-    load_rows_clamped<HDP>(rv, vbase, ks, key_row(0), Tk, sh.hd, tid);
-    store_rows_masked<HDP, LDK>(smem, rk, tid, key_row(0), Tk, sh.hd);
-    store_rows_masked<HDP, LDV>(smem + KSZ, rv, tid, key_row(0), Tk, sh.hd);
-  }
-  __syncthreads();
-
-  for (int kb = 0; kb < nkb; ++kb) {
-    const int cur = kb & 1;
-    const bool more = kb + 1 < nkb;
-    if (more) {
-      load_rows_clamped<HDP>(rk, kbase, ks, key_row(kb + 1), Tk, sh.hd, tid);
-      load_rows_clamped<HDP>(rv, vbase, ks, key_row(kb + 1), Tk, sh.hd, tid);
-    }
-    const int kp0 = key_pos(kb);
-    if (kp0 <= wpos + 31) {
-      const float* sK = smem + cur * (KSZ + VSZ);
-      const float* sV = sK + KSZ;
-      floatx16 s, dp;
-      zero16(s);
-      zero16(dp);
-      mma_rows_by_reg<HDP, LDK>(s, sK, qf, lr, hh);    // S^T  [key][q]
-      mma_rows_by_reg<HDP, LDV>(dp, sV, dof, lr, hh);  // dP^T [key][q]
-      const int kr0 = key_row(kb);
-      if ((kp0 + 31 > wpos) || (kr0 + 32 > Tk)) {  // diagonal or ragged tile (uniform)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kk = acc_row(r, hh);
-          const bool dead = (kp0 + kk > my_qpos) | (kr0 + kk >= Tk);
-          const float p = dead ? 0.f : exp2_hw(s[r] - lse2);
-          s[r] = p * (dp[r] - Dq);  // dS^T
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = exp2_hw(s[r] - lse2) * (dp[r] - Dq);
-      }
-      mma_tile_T_by_acc<HDP, LDK>(dq, sK, s, lr, hh);  // dQ^T[d][q] += K^T dS^T
-    }
-    if (more) {
-      float* sN = smem + (cur ^ 1) * (KSZ + VSZ);
-      store_rows_masked<HDP, LDK>(sN, rk, tid, key_row(kb + 1), Tk, sh.hd);
-      store_rows_masked<HDP, LDV>(sN + KSZ, rv, tid, key_row(kb + 1), Tk, sh.hd);
-    }
-    __syncthreads();
-  }
-  float* stage = smem + wave * 32 * (HDP + 4);
+  const bool fits = ks < FORM_STRIDE;
+  if (fits)
+    dq_pass_split<HDP, SEG>(dq, smem, qbase, rs, dobase, kbase, ks, C, sh.T, Tk, sh.hd, sm_scale, lse2, Dq, my_q, wpos,
+                          kt, tid);
+  if (__builtin_expect(!fits || __syncthreads_or(needs_f32(dq, 0.f)), 0))
+    dq_pass_f32<HDP, SEG>(dq, reinterpret_cast<float*>(smem), qbase, rs, dobase, kbase, ks, C, sh.T, Tk, sh.hd,
+                          sm_scale, lse2, Dq, my_q, wpos, kt, tid);
+  float* stage = reinterpret_cast<float*>(smem) + wave * 32 * (HDP + 4);
   float* dqbase = dqkv + (long long)b * sh.T * rs + (long long)h * sh.hd;
   store_T_tile<HDP>(stage, dq, sm_scale, dqbase, rs, qw0, sh.T, sh.hd, lane,
                     SEG && (sg.flags & SEG_ACC_DQ));
@@ -666,18 +936,234 @@ __global__ void __launch_bounds__(256) attn_bwd_d_kernel(const float* __restrict
 // SEG: keys and values from sg.kv, dK/dV to sg.dkv (optionally added), queries
 // visible by segment positions; dS ([B, H, T, Tk]) when positions are
 // multiples of 128 (the segmented dQ product's tiles).
-template <int HDP, bool SEG>
+
+// One wave's 32 keys and the query tiles they are visible to.
+template <bool SEG>
+struct DkvWave {
+  const float *qbase, *dobase, *kbase, *vbase, *lrow, *drow;
+  float* ds_bh;  // dS / sqrt(hd) of this (b, h), or null
+  long long rs, ks;
+  int C, T, Tk, hd, kw0, my_k, kwpos, my_kpos;
+  int qb0, nq, c0, m1;
+  float sm_scale;
+  unsigned ds_voff;
+  const AttnSegs& sg;
+  __device__ int q_row(int j) const {
+    return SEG ? (j < c0 ? 32 * (qb0 + j) : sg.seg + 32 * (m1 + j - c0)) : 32 * (qb0 + j);
+  }
+  __device__ int q_pos(int j) const {
+    return SEG ? (j < c0 ? sg.q_pos[0] + 32 * (qb0 + j) : sg.q_pos[1] + 32 * (m1 + j - c0)) : 32 * (qb0 + j);
+  }
+  // P = exp(S - lse) in place of the scores of one 32 x 32 block [q][key].
+  __device__ __forceinline__ void probabilities(floatx16& s, const float* sl, int qp, int hh) const {
+    if ((qp < kwpos + 31) || (kw0 + 32 > Tk)) {  // diagonal or ragged tile (uniform)
+      asm volatile("");  // a branch, not selects
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int qi = acc_row(r, hh);
+        const bool dead = (my_kpos > qp + qi) | (my_k >= Tk);
+        s[r] = dead ? 0.f : exp2_hw(s[r] - sl[qi]);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = exp2_hw(s[r] - sl[acc_row(r, hh)]);
+    }
+  }
+  // dS of one query tile to the workspace.  One buffer resource per query
+  // tile, limited to the tile's rows below T: the stores of rows past T fall
+  // outside it and are dropped.  The tile base and the per-register offsets
+  // are scalars, so the 16 stores need no vector address arithmetic.  Query
+  // tiles of the diagonal 128-row tile that precede this wave's keys are fully
+  // masked and stored as zeros, because the dQ product of that tile sums keys
+  // up to the tile's end.
+  __device__ __forceinline__ void store_ds(const floatx16& dp, bool live, int qv0, int qp) const {
+    if (!(ds_bh && my_k < Tk && (live || qp < kwpos))) return;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ds_bh + (long long)qv0 * Tk, (short)0,
+                                                        4 * Tk * min(32, T - qv0), 0x00020000);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, live ? dp[r] * sm_scale : 0.f), rsrc,
+                                            ds_voff, 4 * Tk * (8 * (r >> 2) + (r & 3)), 0);
+  }
+};
+
+// Up to head dim 32 one kernel accumulates dK and dV; beyond, dV and dK (with
+// dS) have one each.  Together they need 290 registers a lane at head dim 64 (K
+// and V as parts 96, sums and small sums 128, scores 32, the rest operands):
+// one wave per SIMD, a third of the vector instructions moves to and from
+// AGPRs, and every wait exposed, 570-590 us at B = 16, T = 1024, 12 heads, no
+// faster than the FP32 instructions (558).  Apart they keep two waves or more
+// per SIMD and share no more than the score products (120 MFMAs per 32 x 32
+// tile instead of 96).
+constexpr int GRAD_V = 1, GRAD_K = 2;
+template <int HDP>
+struct DkvParts {
+  static constexpr bool ONE = HDP <= 32;
+};
+
+// Streamed forms of a query tile: Q rows (S), Q cols (dK), dO rows (dP), dO cols (dV).
+template <int HDP, int GRADS>
+struct QueryForms {
+  static constexpr bool V = (GRADS & GRAD_V) != 0, K = (GRADS & GRAD_K) != 0;
+  static constexpr int Q_COLS = 1, DO_ROWS = Q_COLS + (K ? 1 : 0), DO_COLS = DO_ROWS + (K ? 1 : 0);
+  static constexpr int N = DO_COLS + (V ? 1 : 0);
+  static constexpr int BUF = N * FragForm<HDP>::BYTES + 256;  // the forms, lse2[32], D[32]
+};
+
+template <int HDP, bool SEG, int GRADS>
+__device__ __forceinline__ void dkv_pass_split(floatx16 (&dk)[HDP / 32], floatx16 (&dv)[HDP / 32], char* smem,
+                                               const DkvWave<SEG>& w, int tid) {
+  using F = FragForm<HDP>;
+  using QF = QueryForms<HDP, GRADS>;
+  const int lane = tid & 63, hh = lane >> 5;
+  Split8 kf[HDP / 16], vf[QF::K ? HDP / 16 : 1];
+  load_split_operand<HDP>(kf, w.kbase, w.ks, w.my_k, w.Tk, w.hd, hh, LOG2E * w.sm_scale);
+  if constexpr (QF::K) load_split_operand<HDP>(vf, w.vbase, w.ks, w.my_k, w.Tk, w.hd, hh, 1.f);
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) {
+    zero16(dk[db]);
+    zero16(dv[db]);
+  }
+  floatx16 dv_small[HDP / 32];
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) zero16(dv_small[db]);
+  constexpr bool LAST = GRADS == GRAD_V;  // room for small sums over all tiles
+  float rf[QF::N][F::SU][8];
+  float rl = 0.f, rd = 0.f;
+  const FormLoad<HDP, false> qr(w.rs, w.hd, tid), gr(w.C, w.hd, tid);
+  const FormLoad<HDP, true> qc(w.rs, w.hd, tid), gc(w.C, w.hd, tid);
+  auto load_q = [&](int j) {
+    const long long r0 = w.q_row(j);
+    const int rows = w.T - (int)r0;
+    qr.load(rf[0], w.qbase + r0 * w.rs, rows, tid);
+    if constexpr (QF::K) {
+      qc.load(rf[QF::Q_COLS], w.qbase + r0 * w.rs, rows, tid);
+      gr.load(rf[QF::DO_ROWS], w.dobase + r0 * w.C, rows, tid);
+    }
+    if constexpr (QF::V) gc.load(rf[QF::DO_COLS], w.dobase + r0 * w.C, rows, tid);
+    if (tid < 32) {
+      const int t = min((int)r0 + tid, w.T - 1);
+      rl = w.lrow[t];
+      if (QF::K) rd = w.drow[t];
+    }
+  };
+  auto store_q = [&](char* buf, int j) {
+#pragma unroll
+    for (int f = 0; f < QF::N; ++f) store_form<HDP>(buf + f * F::BYTES, rf[f], tid);
+    if (tid < 32) {
+      const bool ok = w.q_row(j) + tid < w.T;
+      float* sl = reinterpret_cast<float*>(buf + QF::N * F::BYTES);
+      sl[tid] = ok ? rl * LOG2E : INFINITY;  // rows past T give P = 0
+      if (QF::K) sl[32 + tid] = ok ? rd : 0.f;
+    }
+  };
+  if (w.nq > 0) {
+    load_q(0);
+    store_q(smem, 0);
+  }
+  __syncthreads();
+  for (int j = 0; j < w.nq; ++j) {
+    const char* cur = smem + (j & 1) * QF::BUF;
+    const bool more = j + 1 < w.nq;
+    if (more) load_q(j + 1);
+    const int qv0 = w.q_row(j);  // first row of the query tile
+    const int qp = w.q_pos(j);   // its first position
+    const bool live = qp + 31 >= w.kwpos && w.kw0 < w.Tk;  // some query of the tile sees this wave's keys
+    floatx16 dp;
+    if (live) {
+      const float* sl = reinterpret_cast<const float*>(cur + QF::N * F::BYTES);
+      const float* sd = sl + 32;
+      floatx16 s;
+      split_rows_by_reg<HDP>(s, cur, kf, lane);  // S  [q][key]
+      // P needs only S: it is formed while the dP products run
+      if constexpr (QF::K) split_rows_by_reg<HDP>(dp, cur + QF::DO_ROWS * F::BYTES, vf, lane);  // dP [q][key]
+      w.probabilities(s, sl, qp, hh);
+      if constexpr (QF::V)  // dV^T[d][key] += dO^T P
+        split_tile_T_by_acc<HDP>(dv, LAST ? &dv_small : nullptr, cur + QF::DO_COLS * F::BYTES, s, lane);
+      if constexpr (QF::K) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dp[r] = s[r] * (dp[r] - sd[acc_row(r, hh)]);  // dS
+        split_tile_T_by_acc<HDP>(dk, nullptr, cur + QF::Q_COLS * F::BYTES, dp, lane);  // dK^T[d][key] += Q^T dS
+      }
+    }
+    // The next tile goes to LDS before this tile's dS is stored: loads and
+    // stores retire in order on one counter, so a wait for the next tile's
+    // loads issued after the stores would also wait for the stores to be
+    // written.
+    if (more) store_q(smem + ((j + 1) & 1) * QF::BUF, j + 1);
+    if constexpr (QF::K) w.store_ds(dp, live, qv0, qp);
+    __syncthreads();
+  }
+  if (LAST) {
+#pragma unroll
+    for (int db = 0; db < HDP / 32; ++db) dv[db] += dv_small[db];
+  }
+}
+
+template <int HDP, bool SEG, int GRADS>
+__device__ __forceinline__ void dkv_pass_f32(floatx16 (&dk)[HDP / 32], floatx16 (&dv)[HDP / 32], float* smem,
+                                             const DkvWave<SEG>& w, int tid) {
+  constexpr bool GV = (GRADS & GRAD_V) != 0, GK = (GRADS & GRAD_K) != 0;
+  constexpr int LD = HDP + 4;
+  constexpr int TSZ = 32 * LD;
+  const int lane = tid & 63, lr = lane & 31, hh = lane >> 5;
+  float kf[HDP / 2], vf[HDP / 2];
+  load_reg_operand<HDP>(kf, w.kbase, w.ks, w.my_k, w.Tk, w.hd, hh, LOG2E * w.sm_scale);
+  if (GK) load_reg_operand<HDP>(vf, w.vbase, w.ks, w.my_k, w.Tk, w.hd, hh, 1.f);
+#pragma unroll
+  for (int db = 0; db < HDP / 32; ++db) {
+    zero16(dk[db]);
+    zero16(dv[db]);
+  }
+  float* sl = smem + 2 * TSZ;
+  float* sd = sl + 32;
+  for (int j = 0; j < w.nq; ++j) {
+    const int qv0 = w.q_row(j), qp = w.q_pos(j);
+    floatx4 rq[HDP / 32], rdo[HDP / 32];
+    load_rows_clamped<HDP>(rq, w.qbase, w.rs, qv0, w.T, w.hd, tid);
+    load_rows_clamped<HDP>(rdo, w.dobase, w.C, qv0, w.T, w.hd, tid);
+    __syncthreads();
+    store_rows_masked<HDP, LD>(smem, rq, tid, qv0, w.T, w.hd);
+    store_rows_masked<HDP, LD>(smem + TSZ, rdo, tid, qv0, w.T, w.hd);
+    if (tid < 32) {
+      const bool ok = qv0 + tid < w.T;
+      const int t = min(qv0 + tid, w.T - 1);
+      sl[tid] = ok ? w.lrow[t] * LOG2E : INFINITY;
+      sd[tid] = ok ? w.drow[t] : 0.f;
+    }
+    __syncthreads();
+    const bool live = qp + 31 >= w.kwpos && w.kw0 < w.Tk;
+    floatx16 dp;
+    if (live) {
+      floatx16 s;
+      zero16(s);
+      zero16(dp);
+      mma_rows_by_reg<HDP, LD>(s, smem, kf, lr, hh);
+      if (GK) mma_rows_by_reg<HDP, LD>(dp, smem + TSZ, vf, lr, hh);
+      w.probabilities(s, sl, qp, hh);
+      if (GV) mma_tile_T_by_acc<HDP, LD>(dv, smem + TSZ, s, lr, hh);
+      if (GK) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dp[r] = s[r] * (dp[r] - sd[acc_row(r, hh)]);
+        mma_tile_T_by_acc<HDP, LD>(dk, smem, dp, lr, hh);
+      }
+    }
+    if (GK) w.store_ds(dp, live, qv0, qp);
+  }
+  __syncthreads();
+}
+
+template <int HDP, bool SEG, int GRADS>
 __global__ void __launch_bounds__(256, HDP <= 64 ? 2 : 1) attn_bwd_dkv_kernel(
     const float* __restrict__ dout, const float* __restrict__ qkv, const float* __restrict__ lse,
     const float* __restrict__ Dws, float* __restrict__ dqkv, float* __restrict__ dS, AttnShape sh,
     AttnSegs sg) {
-  constexpr int LD = HDP + 4;
-  constexpr int TSZ = 32 * LD;
-  // per buffer: Q tile, dO tile, lse2[32], D[32]
-  constexpr int BUF = 2 * TSZ + 64;
-  __shared__ __attribute__((aligned(16))) float smem[2 * BUF];
+  constexpr int SMEM_SPLIT = 2 * QueryForms<HDP, GRADS>::BUF;
+  constexpr int SMEM_F32 = 4 * (2 * 32 * (HDP + 4) + 64), SMEM_OUT = 4 * 4 * 32 * (HDP + 4);
+  constexpr int SMEM_REST = SMEM_F32 > SMEM_OUT ? SMEM_F32 : SMEM_OUT;
+  __shared__ __attribute__((aligned(16))) char smem[SMEM_SPLIT > SMEM_REST ? SMEM_SPLIT : SMEM_REST];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, hh = lane >> 5;
   const int BH = sh.B * sh.H;
   const int kt = (int)(blockIdx.x / BH);  // low key tiles see the most queries: first
@@ -689,38 +1175,13 @@ __global__ void __launch_bounds__(256, HDP <= 64 ? 2 : 1) attn_bwd_dkv_kernel(
   const long long ks = SEG ? sg.kv_stride : rs;
   const float* qbase = qkv + (long long)b * sh.T * rs + (long long)h * sh.hd;
   const float* kbase = SEG ? sg.kv + (long long)b * Tk * ks + (long long)h * sh.hd : qbase + C;
-  const float* vbase = kbase + C;
-  const float* dobase = dout + (long long)b * sh.T * C + (long long)h * sh.hd;
-  const float* lrow = lse + (long long)bh * sh.T;
-  const float* drow = Dws + (long long)bh * sh.T;
 
   const int k0 = kt * 128;
   const int kw0 = k0 + 32 * wave;
-  const int my_k = kw0 + lr;
   const int kp0 = SEG ? seg_pos(sg.k_pos, sg.seg, k0) : k0;  // the block's rows lie in one segment
-  const int kwpos = kp0 + 32 * wave;
-  const int my_kpos = kwpos + lr;
   const float sm_scale = 1.f / sqrtf((float)sh.hd);
-  // dS / sqrt(hd) for the dQ product, [B, H, T, Tk]: this (b, h)'s rows, and
-  // the byte offset of this lane's first element in a query tile (row 4 hh,
-  // column my_k); register r of the tile is a scalar offset further.
-  float* const ds_bh = dS ? dS + (long long)bh * sh.T * Tk : nullptr;
-  const bool ds_lane = my_k < Tk;
-  const unsigned ds_voff = 4u * (unsigned)(4 * hh * Tk + my_k);
-
-  float kf[HDP / 2], vf[HDP / 2];
-  load_reg_operand<HDP>(kf, kbase, ks, my_k, Tk, sh.hd, hh, LOG2E * sm_scale);
-  load_reg_operand<HDP>(vf, vbase, ks, my_k, Tk, sh.hd, hh, 1.f);
-
-  floatx16 dk[HDP / 32], dv[HDP / 32];
-#pragma unroll
-  for (int db = 0; db < HDP / 32; ++db) {
-    zero16(dk[db]);
-    zero16(dv[db]);
-  }
-
   // streamed query tiles: causal, rows from the key tile's diagonal to the
-  // end; SEG, a suffix of each query segment (c0 tiles of the first, from m0)
+  // end; SEG, a suffix of each query segment (c0 tiles of the first, from m1)
   int qb0, nq, c0, m1 = 0;
   if (SEG) {
     const int per = sg.seg / 32;
@@ -736,104 +1197,48 @@ __global__ void __launch_bounds__(256, HDP <= 64 ? 2 : 1) attn_bwd_dkv_kernel(
     nq = max(0, (sh.T + 31) / 32 - qb0);
     c0 = nq;
   }
-  auto q_row = [&](int j) { return SEG ? (j < c0 ? 32 * (qb0 + j) : sg.seg + 32 * (m1 + j - c0)) : 32 * (qb0 + j); };
-  auto q_pos = [&](int j) {
-    return SEG ? (j < c0 ? sg.q_pos[0] + 32 * (qb0 + j) : sg.q_pos[1] + 32 * (m1 + j - c0)) : 32 * (qb0 + j);
-  };
+  const int my_k = kw0 + lr, kwpos = kp0 + 32 * wave;
+  // dS: this (b, h)'s rows, and the byte offset of this lane's first element
+  // in a query tile (row 4 hh, column my_k); register r of the tile is a
+  // scalar offset further
+  const DkvWave<SEG> w{qbase,
+                       dout + (long long)b * sh.T * C + (long long)h * sh.hd,
+                       kbase,
+                       kbase + C,
+                       lse + (long long)bh * sh.T,
+                       Dws + (long long)bh * sh.T,
+                       dS ? dS + (long long)bh * sh.T * Tk : nullptr,
+                       rs,
+                       ks,
+                       C,
+                       sh.T,
+                       Tk,
+                       sh.hd,
+                       kw0,
+                       my_k,
+                       kwpos,
+                       kwpos + lr,
+                       qb0,
+                       nq,
+                       c0,
+                       m1,
+                       sm_scale,
+                       4u * (unsigned)(4 * hh * Tk + my_k),
+                       sg};
+  floatx16 dk[HDP / 32], dv[HDP / 32];
+  constexpr bool GV = (GRADS & GRAD_V) != 0, GK = (GRADS & GRAD_K) != 0;
+  const bool fits = rs < FORM_STRIDE;
+  if (fits) dkv_pass_split<HDP, SEG, GRADS>(dk, dv, smem, w, tid);
+  if (__builtin_expect(!fits || __syncthreads_or((GK && needs_f32(dk, 0.f)) || (GV && needs_f32(dv, 0.f))), 0))
+    dkv_pass_f32<HDP, SEG, GRADS>(dk, dv, reinterpret_cast<float*>(smem), w, tid);
 
-  floatx4 rq[HDP / 32], rdo[HDP / 32];
-  float rl = 0.f, rd = 0.f;
-  auto load_q = [&](int j) {
-    const int r0 = q_row(j);
-    load_rows_clamped<HDP>(rq, qbase, rs, r0, sh.T, sh.hd, tid);
-    load_rows_clamped<HDP>(rdo, dobase, C, r0, sh.T, sh.hd, tid);
-    if (tid < 32) {
-      const int t = min(r0 + tid, sh.T - 1);
-      rl = lrow[t];
-      rd = drow[t];
-    }
-  };
-  auto store_q = [&](float* sb, int j) {
-    const int r0 = q_row(j);
-    store_rows_masked<HDP, LD>(sb, rq, tid, r0, sh.T, sh.hd);
-    store_rows_masked<HDP, LD>(sb + TSZ, rdo, tid, r0, sh.T, sh.hd);
-    if (tid < 32) {
-      const bool ok = r0 + tid < sh.T;
-      sb[2 * TSZ + tid] = ok ? rl * LOG2E : INFINITY;  // rows past T give P = 0
-      sb[2 * TSZ + 32 + tid] = ok ? rd : 0.f;
-    }
-  };
-  if (nq > 0) {
-    load_q(0);
-    store_q(smem, 0);
-  }
-  __syncthreads();
-
-  for (int j = 0; j < nq; ++j) {
-    const int cur = j & 1;
-    const bool more = j + 1 < nq;
-    if (more) load_q(j + 1);
-    const int qv0 = q_row(j);   // first row of the query tile
-    const int qp = q_pos(j);    // its first position
-    const bool live = qp + 31 >= kwpos && kw0 < Tk;  // some query of the tile sees this wave's keys
-    floatx16 dp;
-    if (live) {
-      const float* sQ = smem + cur * BUF;
-      const float* sdO = sQ + TSZ;
-      const float* sl = sQ + 2 * TSZ;
-      const float* sd = sl + 32;
-      floatx16 s;
-      zero16(s);
-      zero16(dp);
-      mma_rows_by_reg<HDP, LD>(s, sQ, kf, lr, hh);    // S  [q][key]
-      mma_rows_by_reg<HDP, LD>(dp, sdO, vf, lr, hh);  // dP [q][key]
-      // P needs only S: it is formed while the dP products run, and the dV
-      // products (which need only P) run while dS is formed.
-      if ((qp < kwpos + 31) || (kw0 + 32 > Tk)) {  // diagonal or ragged tile (uniform)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int qi = acc_row(r, hh);
-          const bool dead = (my_kpos > qp + qi) | (my_k >= Tk);
-          s[r] = dead ? 0.f : exp2_hw(s[r] - sl[qi]);
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = exp2_hw(s[r] - sl[acc_row(r, hh)]);
-      }
-      mma_tile_T_by_acc<HDP, LD>(dv, sdO, s, lr, hh);  // dV^T[d][key] += dO^T P
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dp[r] = s[r] * (dp[r] - sd[acc_row(r, hh)]);  // dS
-      mma_tile_T_by_acc<HDP, LD>(dk, sQ, dp, lr, hh);  // dK^T[d][key] += Q^T dS
-    }
-    // The next tile goes to LDS before this tile's dS is stored: loads and
-    // stores retire in order on one counter, so a wait for the next tile's
-    // loads issued after the stores would also wait for the stores to be
-    // written.
-    if (more) store_q(smem + (cur ^ 1) * BUF, j + 1);
-    if (ds_bh && ds_lane && (live || qp < kwpos)) {
-      // One buffer resource per query tile, limited to the tile's rows below
-      // T: the stores of rows past T fall outside it and are dropped.  The
-      // tile base and the per-register offsets are scalars, so the 16
-      // stores need no vector address arithmetic.  Query tiles of the
-      // diagonal 128-row tile that precede this wave's keys are fully masked
-      // and stored as zeros, because the dQ product of that tile sums keys
-      // up to the tile's end.
-      const auto rs = __builtin_amdgcn_make_buffer_rsrc(ds_bh + (long long)qv0 * Tk, (short)0,
-                                                        4 * Tk * min(32, sh.T - qv0), 0x00020000);
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, live ? dp[r] * sm_scale : 0.f), rs,
-                                              ds_voff, 4 * Tk * (8 * (r >> 2) + (r & 3)), 0);
-    }
-    __syncthreads();
-  }
-  float* stage = smem + wave * 32 * (HDP + 4);
+  float* stage = reinterpret_cast<float*>(smem) + wave * 32 * (HDP + 4);
   float* dkbase = SEG ? sg.dkv + (long long)b * Tk * ks + (long long)h * sh.hd
                       : dqkv + (long long)b * sh.T * rs + (long long)h * sh.hd + C;
   const bool add = SEG && (sg.flags & SEG_ACC_DKV);
-  store_T_tile<HDP>(stage, dk, sm_scale, dkbase, ks, kw0, Tk, sh.hd, lane, add);
-  __syncthreads();
-  store_T_tile<HDP>(stage, dv, 1.f, dkbase + C, ks, kw0, Tk, sh.hd, lane, add);
+  if (GK) store_T_tile<HDP>(stage, dk, sm_scale, dkbase, ks, kw0, Tk, sh.hd, lane, add);
+  if (GK && GV) __syncthreads();
+  if (GV) store_T_tile<HDP>(stage, dv, 1.f, dkbase + C, ks, kw0, Tk, sh.hd, lane, add);
 }
 
 bt_status check_attn(const void* a, const void* b2, int B, int T, int H, int hd, const char* who) {
@@ -851,14 +1256,8 @@ void launch_fwd(int hd, dim3 grid, hipStream_t s, const float* qkv, float* out, 
                 const AttnShape& sh, const AttnSegs& sg) {
   if (hd <= 32)
     hipLaunchKernelGGL((attn_fwd_kernel<32, SEG>), grid, dim3(256), 0, s, qkv, out, lse, sh, sg);
-  else if (hd <= 64) {
-    // direct-to-LDS key / value tiles when every key tile is full and the
-    // per-lane copy offsets (32 rows of the token stride) fit in 32 bits
-    if (!SEG && hd == 64 && sh.T % 32 == 0 && sh.row_stride < (1LL << 24))
-      hipLaunchKernelGGL((attn_fwd_kernel<64, false, true>), grid, dim3(256), 0, s, qkv, out, lse, sh, sg);
-    else
-      hipLaunchKernelGGL((attn_fwd_kernel<64, SEG>), grid, dim3(256), 0, s, qkv, out, lse, sh, sg);
-  }
+  else if (hd <= 64)
+    hipLaunchKernelGGL((attn_fwd_kernel<64, SEG>), grid, dim3(256), 0, s, qkv, out, lse, sh, sg);
   else
     hipLaunchKernelGGL((attn_fwd_kernel<128, SEG>), grid, dim3(256), 0, s, qkv, out, lse, sh, sg);
 }
@@ -874,15 +1273,26 @@ void launch_dq(int hd, dim3 grid, hipStream_t s, const float* dout, const float*
     hipLaunchKernelGGL((attn_bwd_dq_kernel<128, SEG>), grid, dim3(256), 0, s, dout, qkv, out, lse, dqkv, D, sh, sg);
 }
 
+template <int HDP, bool SEG>
+void launch_dkv_hd(dim3 grid, hipStream_t s, const float* dout, const float* qkv, const float* lse, const float* D,
+                   float* dqkv, float* dS, const AttnShape& sh, const AttnSegs& sg) {
+  if constexpr (DkvParts<HDP>::ONE) {
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<HDP, SEG, GRAD_K | GRAD_V>), grid, dim3(256), 0, s, dout, qkv, lse, D,
+                       dqkv, dS, sh, sg);
+  } else {
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<HDP, SEG, GRAD_K>), grid, dim3(256), 0, s, dout, qkv, lse, D, dqkv, dS, sh,
+                       sg);
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<HDP, SEG, GRAD_V>), grid, dim3(256), 0, s, dout, qkv, lse, D, dqkv, dS, sh,
+                       sg);
+  }
+}
+
 template <bool SEG>
 void launch_dkv(int hd, dim3 grid, hipStream_t s, const float* dout, const float* qkv, const float* lse,
                 const float* D, float* dqkv, float* dS, const AttnShape& sh, const AttnSegs& sg) {
-  if (hd <= 32)
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<32, SEG>), grid, dim3(256), 0, s, dout, qkv, lse, D, dqkv, dS, sh, sg);
-  else if (hd <= 64)
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<64, SEG>), grid, dim3(256), 0, s, dout, qkv, lse, D, dqkv, dS, sh, sg);
-  else
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<128, SEG>), grid, dim3(256), 0, s, dout, qkv, lse, D, dqkv, dS, sh, sg);
+  if (hd <= 32) launch_dkv_hd<32, SEG>(grid, s, dout, qkv, lse, D, dqkv, dS, sh, sg);
+  else if (hd <= 64) launch_dkv_hd<64, SEG>(grid, s, dout, qkv, lse, D, dqkv, dS, sh, sg);
+  else launch_dkv_hd<128, SEG>(grid, s, dout, qkv, lse, D, dqkv, dS, sh, sg);
 }
 
 bt_status launch_d(const float* dout, const float* out, float* D, int B, int T, int H, int hd, hipStream_t s) {

@@ -14,11 +14,11 @@
 // and are left out (bt_internal.h): six BF16 products, 417 TFLOP/s at the
 // nominal rate.  On MI355X dense BF16 work on random data is limited by power,
 // not by issue: six-product chains from registers alone run at 380 TFLOP/s
-// with 16x16x32 MFMAs and at 303 with 32x32x16 ones (the clock falls from
-// 2.35 to 1.7 GHz; with zero operands both run at 410), so the kernel is laid
+// with 16x16x32 MFMAs, and 32x32x16 ones at a rate worth 308 (with zero
+// operands both reach 407-413), so the kernel is laid
 // out to spend little energy beside the MFMAs:
 //  * 16x16x32 MFMAs, the six products of an accumulator back to back
-//    (384 against 348 TFLOP/s with the accumulators interleaved);
+//    (384 against 354 TFLOP/s with the accumulators interleaved);
 //  * a block tile of 256 x 192 on one CU: 8 waves of 32 x 192 outputs.  Each
 //    wave loads its own 32 rows of op(A) from global memory straight into
 //    registers and splits them there: A never passes through LDS, and no
@@ -27,14 +27,15 @@
 //    for its additional loads; FP32 tiles in LDS split by every wave that
 //    reads them reached 180-215 TFLOP/s against 214-246 here;
 //  * the B tile in LDS is stored as the MFMA reads it (1 KB of one part's
-//    16 x 32 fragment, lane by lane), so reads are linear and free of
-//    conflicts; its parts are read once per fragment and wave.
+//    16 x 32 fragment, lane by lane), so reads are linear; its parts are read
+//    once per fragment and wave.  Bank conflicts take 17% of the LDS cycles,
+//    under 5% of all.
 // The split of the next k-tile (5.5 vector instructions per value) is spread
 // evenly between the MFMAs of this one: 2 of them per MFMA hide completely
-// with two waves per SIMD, but the same work in one burst per k-tile cost 13%
-// of the cycles.  At 16384 x 768 x 3072 (NT) the matrix pipe is busy in 77%
-// of the cycles; 246 TFLOP/s on random data, 309 on zeros (FP32 instructions:
-// 138 on both).
+// with two waves per SIMD (register-only chains: 2414 against 2419 TFLOP/s on
+// zeros), but in bursts after every 6 or 24 MFMAs they cost 20% and 8%.  At 16384 x 768 x 3072 (NT) the matrix pipe is busy in 73%
+// of the cycles; 237 TFLOP/s at 1.87 GHz on random data, 300 at 2.33 GHz on
+// zeros (counters on; FP32 instructions: 138).
 //
 // Three LDS buffers (256-row tiles) let one barrier in mid-tile order writes
 // and reads; the fragments of the next k-tile are then read ahead of its

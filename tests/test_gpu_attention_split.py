@@ -1,0 +1,136 @@
+"""Edges of the attention kernels' split products (FP32 operands as three BF16
+parts): every padded head dim from both sides, ragged lengths, and inputs that
+the parts cannot represent, which a block computes again in FP32.
+
+Reference: torch in float64 on the GPU.  Error bar: scores round by about
+2^-23 sum |q||k| / sqrt(hd), at most 1e-6 for these inputs, and enter results
+as relative errors of the probabilities; sums over T <= 300 keys and hd <= 128
+add less than 2^-23 sqrt(T) each.  1e-5 of the largest value of a tensor is
+about four times what that gives."""
+import math
+
+import pytest
+
+from paper_2606_24780_amd import bt
+from tests.gpu_util import say, torch_gpu
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def _reference(torch, qkv, dout, B, T, H, hd):
+    q, k, v = (t.permute(0, 2, 1, 3).contiguous() for t in qkv.double().reshape(B, T, 3, H, hd).unbind(2))
+    g = dout.double().reshape(B, T, H, hd).permute(0, 2, 1, 3).contiguous()
+    scale = 1.0 / math.sqrt(hd)
+    dead = torch.ones((T, T), dtype=torch.bool, device="cuda").triu(1)
+    S = (q @ k.transpose(2, 3).contiguous() * scale).masked_fill(dead, -math.inf)
+    m = S.amax(-1, keepdim=True)
+    e = (S - m).exp()
+    l = e.sum(-1, keepdim=True)
+    P = e / l
+    O = P @ v
+    dV = P.transpose(2, 3).contiguous() @ g
+    dP = g @ v.transpose(2, 3).contiguous()
+    dS = P * (dP - (g * O).sum(-1, keepdim=True)) * scale
+    dQ, dK = dS @ k, dS.transpose(2, 3).contiguous() @ q
+    rows = lambda t: t.permute(0, 2, 1, 3)  # noqa: E731
+    return rows(O).reshape(B * T, H * hd), (m + l.log()).squeeze(-1), torch.stack([rows(dQ), rows(dK), rows(dV)], 2)
+
+
+def _run(torch, qkv, dout, B, T, H, hd, small_ws=False):
+    out, lse = torch.empty((B * T, H * hd), device="cuda"), torch.empty((B, H, T), device="cuda")
+    dqkv = torch.full((B * T, 3 * H * hd), float("nan"), device="cuda")
+    bt.bt_attention_fwd(qkv, out, lse, B, T, H, hd)
+    bt.bt_attention_bwd(dout, qkv, out, lse, dqkv, B, T, H, hd, small_ws=small_ws)
+    torch.cuda.synchronize()
+    return out, lse, dqkv.reshape(B, T, 3, H, hd)
+
+
+def _close(got, ref, what, scale=None):
+    err = (got.double() - ref).abs().max().item()
+    scale = scale or ref.abs().max().item()
+    assert err <= TOL * scale, f"{what}: {err:.3e} > {TOL} of {scale:.3e}"
+
+
+@pytest.mark.parametrize("hd", [4, 28, 32, 36, 60, 64, 68, 100, 128])
+@pytest.mark.parametrize("T", [4, 33, 128, 300])
+def test_head_dims_and_lengths(hd, T):
+    torch = torch_gpu()
+    B, H = 2, 2
+    say(f"attention split hd={hd} T={T}")
+    g = torch.Generator(device="cuda").manual_seed(hd + T)
+    qkv = torch.randn((B * T, 3 * H * hd), generator=g, device="cuda")
+    dout = torch.randn((B * T, H * hd), generator=g, device="cuda")
+    ro, rl, rd = _reference(torch, qkv, dout, B, T, H, hd)
+    for small in (False, True):
+        out, lse, dqkv = _run(torch, qkv, dout, B, T, H, hd, small)
+        _close(out, ro, "out")
+        _close(lse, rl, "lse")
+        for i, n in enumerate(("dq", "dk", "dv")):
+            _close(dqkv[:, :, i], rd[:, :, i], n)
+
+
+def test_long_rows_move_the_running_maximum():
+    """Scores that grow along the keys by far more than 2^8 per tile: the lazily
+    moved maximum has to follow."""
+    torch = torch_gpu()
+    B, T, H, hd = 1, 260, 1, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    qkv = torch.randn((T, 3, hd), generator=g, device="cuda")
+    qkv[:, 0] = qkv[:, 0].abs()
+    qkv[:, 1] = qkv[:, 1].abs() * torch.linspace(0.1, 40, T, device="cuda")[:, None]
+    qkv = qkv.reshape(T, 3 * hd).contiguous()
+    dout = torch.randn((T, hd), generator=g, device="cuda")
+    ro, rl, rd = _reference(torch, qkv, dout, B, T, H, hd)
+    out, lse, _ = _run(torch, qkv, dout, B, T, H, hd)
+    # scores up to about 200: their rounding is a relative error of P
+    assert (out.double() - ro).abs().max() <= 2e-4 * ro.abs().max()
+    _close(lse, rl, "lse")
+
+
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("small", [False, True])
+def test_infinities(hd, small):
+    """Forward results are infinite or NaN exactly where 64-bit arithmetic on
+    the same inputs says so: an infinite value (V), a key with an infinite
+    element (scores +inf: NaN rows; -inf: the key is invisible).  The other
+    head's results and gradients are as ever."""
+    torch = torch_gpu()
+    B, T, H = 1, 196, 3
+    say(f"attention special values hd={hd} small_ws={small}")
+    g = torch.Generator(device="cuda").manual_seed(hd)
+    qkv = torch.randn((T, 3, H, hd), generator=g, device="cuda") * 0.5
+    qkv[64, 2, 0, 3] = float("inf")
+    qkv[96, 1, 1, 2] = float("inf")
+    dout = torch.randn((T, H, hd), generator=g, device="cuda")
+    qkv, dout = qkv.reshape(T, -1).contiguous(), dout.reshape(T, -1).contiguous()
+    ro, rl, rd = _reference(torch, qkv, dout, B, T, H, hd)
+    out, lse, dqkv = _run(torch, qkv, dout, B, T, H, hd, small)
+    # a masked key's infinite value is no part of a row's sum: 0 * inf of the
+    # reference's dense product is taken out of its head
+    ro = ro.reshape(T, H, hd)
+    clean = qkv.reshape(T, 3, H, hd).clone()
+    clean[64, 2, 0, 3] = 0.0
+    ro[:64, 0] = _reference(torch, clean.reshape(T, -1), dout, B, T, H, hd)[0].reshape(T, H, hd)[:64, 0]
+    ro = ro.reshape(T, H * hd)
+    for got, ref, what in ((out, ro, "out"), (lse, rl, "lse"), (dqkv[:, :, :, 2], rd[:, :, :, 2], "dqkv of head 2")):
+        assert torch.equal(torch.isfinite(got), torch.isfinite(ref)), what
+        assert torch.equal(torch.isposinf(got), torch.isposinf(ref)), what
+        ok = torch.isfinite(ref)
+        _close(got[ok], ref[ok], what)
+
+
+def test_tiny_values():
+    """Values of 1e-36: their low parts leave BF16's range.  Each of the T
+    products of a sum may also fall below the smallest normal number, 2^-126,
+    and be flushed."""
+    torch = torch_gpu()
+    B, T, H, hd = 1, 132, 1, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    qkv = torch.randn((T, 3, hd), generator=g, device="cuda")
+    qkv[:, 2] *= 1e-36
+    qkv = qkv.reshape(T, 3 * hd).contiguous()
+    dout = torch.randn((T, hd), generator=g, device="cuda")
+    ro, _, _ = _reference(torch, qkv, dout, B, T, H, hd)
+    out, _, _ = _run(torch, qkv, dout, B, T, H, hd)
+    assert (out.double() - ro).abs().max() <= TOL * ro.abs().max() + T * 2.0**-126

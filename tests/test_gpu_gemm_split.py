@@ -76,6 +76,27 @@ def test_infinities_nan_and_largest_numbers(ta, tb, M, N, K):
     assert ((C - ref).abs()[ok] <= bar[ok]).all()
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [4, 36, 60])
+def test_nothing_past_k_is_read(ta, tb, K):
+    """Operands inside larger buffers whose other elements are NaN: the result
+    is bitwise that of operands inside zeros (a NaN read past the end of K would
+    have its wave repeat the tile in FP32, which rounds differently)."""
+    torch = torch_gpu()
+    M, N, pad = 132, 68, 64
+    g = torch.Generator(device="cuda").manual_seed(K)
+    a = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda")
+    b = torch.randn((N, K) if tb else (K, N), generator=g, device="cuda")
+    out = []
+    for fill in (0.0, float("nan")):
+        A = torch.full((a.shape[0] + pad, a.shape[1] + pad), fill, device="cuda")
+        B = torch.full((b.shape[0] + pad, b.shape[1] + pad), fill, device="cuda")
+        A[:a.shape[0], :a.shape[1]] = a
+        B[:b.shape[0], :b.shape[1]] = b
+        out.append(_run(torch, ta, tb, M, N, K, A, B))
+    assert torch.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("scale", [1e-30, 1e-36])
 def test_tiny_operand(scale):
     """Operands whose low parts leave BF16's range: repeated in FP32.  Products
