@@ -197,11 +197,12 @@ Launch choose_launch(int M, int N, int K, bool akc, bool bkc, int max_splits) {
 }  // namespace
 
 // Batched causal / segmented product on 128-row block tiles, 64 columns wide
-// for head dims up to 64, else 128.
+// for head dims up to 64 and wide leading dimensions, else 128.
 template <int BMODE>
 static bt_status launch_batched(GemmParams p, hipStream_t stream) {
   constexpr int BM = 128;
-  const int bn = p.N <= 64 ? 64 : 128;
+  const bool wide = !gemm_offsets_fit(p.lda, p.ldb);
+  const int bn = wide || p.N <= 64 ? 64 : 128;
   p.ksplit = (p.K + BK - 1) / BK * BK;
   p.splits = 1;
   p.tiles_m = (p.M + BM - 1) / BM;
@@ -209,7 +210,7 @@ static bt_status launch_batched(GemmParams p, hipStream_t stream) {
   const long long nblocks = (long long)p.tiles_m * p.tiles_n * p.nbatch;
   BT_RETURN_IF(nblocks > 0x7fffffffLL, BT_ESHAPE, "batched product: too many tiles");
   const dim3 grid((unsigned)nblocks), block(256);
-  if (!gemm_offsets_fit(p.lda, p.ldb))
+  if (wide)
     hipLaunchKernelGGL((gemm_f32_mfma<true, false, false, 4, 2, 4, true, BMODE>), grid, block, 0, stream, p);
   else if (bn == 64)
     hipLaunchKernelGGL((gemm_f32_mfma<true, false, false, 4, 2, 4, false, BMODE>), grid, block, 0, stream, p);

@@ -134,3 +134,34 @@ def test_tiny_values():
     ro, _, _ = _reference(torch, qkv, dout, B, T, H, hd)
     out, _, _ = _run(torch, qkv, dout, B, T, H, hd)
     assert (out.double() - ro).abs().max() <= TOL * ro.abs().max() + T * 2.0**-126
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_block_backward_with_wide_key_stride(hd):
+    """A key/value token stride of 2^21 floats: the dQ product reads its keys
+    with 64-bit addresses, in 64-column tiles at every head dim.  Same
+    arithmetic as with packed keys, so within twice the file's error bar."""
+    torch = torch_gpu()
+    B, H, T, W = 1, 1, 512, 2
+    say(f"block backward, wide key stride, hd={hd}")
+    segs = bt.bt_cp_rank_segments(T, W, 1, 0)
+    Tl, C, ld = T // W, H * hd, 1 << 21
+    g = torch.Generator(device="cuda").manual_seed(hd)
+    qkv = torch.randn((B * Tl, 3 * C), generator=g, device="cuda")
+    kv = torch.randn((B * Tl, 2 * C), generator=g, device="cuda")
+    do = torch.randn((B * Tl, C), generator=g, device="cuda")
+    wide = torch.full((B * Tl, ld), float("nan"), device="cuda")
+    wide[:, :2 * C] = kv
+    res = []
+    for keys, ks in ((kv, 2 * C), (wide, ld)):
+        out, lse, D = (torch.empty(s, device="cuda") for s in ((B * Tl, C), (B, H, Tl), (B, H, Tl)))
+        bt.bt_attention_block_fwd(qkv, keys, ks, out, lse, 0, B, H, hd, segs)
+        bt.bt_attention_rowdot(do, out, D, B, Tl, H, hd)
+        dq, dkv = torch.full_like(qkv, float("nan")), torch.zeros((B * Tl, ks), device="cuda")
+        ws = torch.empty(bt.bt_attention_block_bwd_ws_bytes(B, H, hd, segs), dtype=torch.uint8, device="cuda")
+        bt.bt_attention_block_bwd(do, qkv, keys, ks, lse, D, dq, dkv, 0, B, H, hd, segs, ws=ws)
+        torch.cuda.synchronize()
+        res.append((out, dq[:, :C].clone(), dkv[:, :2 * C].clone()))
+    for what, x, y in zip(("out", "dQ", "dK, dV"), *res):
+        err = (x - y).abs().max().item()
+        assert err <= 2 * TOL * x.abs().max().item(), f"{what} {err}"

@@ -128,3 +128,49 @@ def test_results_have_little_bias(K, share):
     B = torch.randn((K, N), generator=g, device="cuda")
     err = _run(torch, 0, 0, M, N, K, A, B).double() - A.double() @ B.double()
     assert err.mean().abs() <= share * err.std(), (err.mean().item(), err.std().item())
+
+
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(68, 60, 32), (260, 3268, 68), (1540, 3908, 36), (3076, 3652, 100),
+                                   (2052, 3844, 68)])
+def test_column_sums_on_every_tile(ta, M, N, K):
+    """One shape per block tile (64x64 up to 256x192), without and with the
+    column sums of op(B): a thread adds its staged values and the block adds
+    the threads', at most K FP32 additions of sum |b| in all."""
+    torch = torch_gpu()
+    say(f"gemm colsum ta={ta} {M}x{N}x{K}")
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda")
+    B = torch.randn((K, N), generator=g, device="cuda")
+    a, b = _op(A, ta), B.double()
+    bar = _bar(K) * (a.abs() @ b.abs())
+    plain = _run(torch, ta, 0, M, N, K, A, B)
+    C = torch.full((M, N), float("nan"), device="cuda")
+    s = torch.full((N,), float("nan"), device="cuda")
+    bt.bt_gemm(ta, 0, M, N, K, A, A.shape[1], B, N, 0.0, C, N, colsum_B=s)
+    torch.cuda.synchronize()
+    assert ((plain.double() - a @ b).abs() <= bar).all() and ((C.double() - a @ b).abs() <= bar).all()
+    assert ((s.double() - b.sum(0)).abs() <= K * 2.0**-24 * b.abs().sum(0)).all()
+
+
+@pytest.mark.parametrize("ta,tb,colsum", [(0, 0, 0), (0, 1, 0), (1, 0, 0), (1, 1, 0), (0, 0, 1), (1, 0, 1)])
+def test_wide_leading_dimensions(ta, tb, colsum):
+    """Leading dimensions from 2^21 floats on take 64-bit addresses: the same
+    products from views with such a row stride."""
+    torch = torch_gpu()
+    M, N, K, ld = 132, 68, 44, 1 << 21
+    say(f"gemm wide ta={ta} tb={tb} colsum={colsum}")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda")
+    B = torch.randn((N, K) if tb else (K, N), generator=g, device="cuda")
+    wa = torch.full((A.shape[0], ld), float("nan"), device="cuda")
+    wb = torch.full((B.shape[0], ld), float("nan"), device="cuda")
+    wa[:, :A.shape[1]], wb[:, :B.shape[1]] = A, B
+    C = torch.full((M, N), float("nan"), device="cuda")
+    s = torch.full((N,), float("nan"), device="cuda") if colsum else None
+    bt.bt_gemm(ta, tb, M, N, K, wa, ld, wb, ld, 0.0, C, N, colsum_B=s)
+    torch.cuda.synchronize()
+    a, b = _op(A, ta), _op(B, tb)
+    assert ((C.double() - a @ b).abs() <= _bar(K) * (a.abs() @ b.abs())).all()
+    if colsum:
+        assert ((s.double() - b.sum(0)).abs() <= K * 2.0**-24 * b.abs().sum(0)).all()
